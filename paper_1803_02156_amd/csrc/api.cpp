@@ -820,13 +820,21 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
         if ((rc = launch_any(H, prec, n_b, kModeSecond, next_args(a, 2, b), geo, s))) return rc;
         // p = 3..n_p: swap(W, U); chebfd_op(H, U, W, X)                  (Alg. 1, recurrence)
         void *Ub = B, *Wb = A;  // after the swap U holds T_2, W holds T_1
+        // X takes the terms of kYTerms steps at a time: in steps 5, 8, ... and the last one
         for (int p = 3; p <= n_p; ++p) {
+            const int pending = (p - 3) % kYTerms + 1;   // terms not yet in X, this step's included
+            const bool update = pending == kYTerms || p == n_p;
             a = base_args(H, alpha, beta);
             a.P = Ub;
             a.O = Wb;
-            a.Y = X;
-            a.g2 = h_gamma[p];
-            if ((rc = launch_any(H, prec, n_b, kModeStep, next_args(a, p, b), geo, s))) return rc;
+            if (update) {
+                a.Y = X;
+                a.y_terms = pending;
+                a.g0 = h_gamma[p - 2];
+                a.g1 = h_gamma[p - 1];
+                a.g2 = h_gamma[p];
+            }
+            if ((rc = launch_any(H, prec, n_b, update ? kModeStep : kModeKpm, next_args(a, p, b), geo, s))) return rc;
             std::swap(Ub, Wb);
         }
     }
@@ -950,6 +958,7 @@ int chebfd_op(const chebfd_matrix *H, double alpha, double beta, double gamma, i
     a.O = d_w;
     a.Y = d_y;
     a.g2 = gamma;
+    a.y_terms = 1;
     a.part_out = static_cast<double *>(d_work);
     a.prog = filter_prog(d_work, n_b, G);
     a.epoch = next_step_epoch();

@@ -168,6 +168,8 @@ __global__ __launch_bounds__(kThreads) void cheb_step_kernel(StepArgs a) {
                 O[e] = nw;
                 if constexpr (MODE == kModeStep) {
                     VT y = Y[e];
+                    if (a.y_terms > 2) y = VT{fma(g0, o.x, y.x), fma(g0, o.y, y.y)};
+                    if (a.y_terms > 1) y = VT{fma(g1, up.x, y.x), fma(g1, up.y, y.y)};
                     y.x = fma(g2, nw.x, y.x);
                     y.y = fma(g2, nw.y, y.y);
                     Y[e] = y;

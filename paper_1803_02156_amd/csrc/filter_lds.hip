@@ -286,8 +286,8 @@ __global__ __launch_bounds__(kThreads) void cheb_lds_kernel(StepArgs a, int tile
                     PK y;
 #pragma unroll
                     for (int c = 0; c < CPL; ++c) {
-                        y.re[c] = fma(g2, nw.re[c], yv.re[c]);
-                        y.im[c] = fma(g2, nw.im[c], yv.im[c]);
+                        y.re[c] = add_terms(a.y_terms, g0, o.re[c], g1, up.re[c], g2, nw.re[c], yv.re[c]);
+                        y.im[c] = add_terms(a.y_terms, g0, o.im[c], g1, up.im[c], g2, nw.im[c], yv.im[c]);
                     }
                     store_pack_nt<T, CPL>(static_cast<T *>(a.Y) + e, y);
                 }

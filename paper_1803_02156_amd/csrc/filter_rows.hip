@@ -202,7 +202,11 @@ __global__ __launch_bounds__(kThreads) void cheb_row_kernel(StepArgs a) {
                 static_cast<T *>(a.Y)[e2] = fma(g0, o_c, fma(g1, up_c, g2 * nw));
             } else {
                 static_cast<T *>(a.O)[e2] = nw;
-                if constexpr (MODE == kModeStep) static_cast<T *>(a.Y)[e2] = fma(g2, nw, y_c);
+                if constexpr (MODE == kModeStep) {
+                    if (a.y_terms > 2) y_c = fma(g0, o_c, y_c);
+                    if (a.y_terms > 1) y_c = fma(g1, up_c, y_c);
+                    static_cast<T *>(a.Y)[e2] = fma(g2, nw, y_c);
+                }
             }
         }
         // eta = sum conj(nw) up: Re from same-component products, Im from the

@@ -349,8 +349,8 @@ __global__ __launch_bounds__(kWinThreads) void cheb_win_kernel(StepArgs a, int64
             } else if constexpr (MODE == kModeStep) {
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    yo.re[c] = fma(g2, nw.re[c], yv.re[c]);
-                    yo.im[c] = fma(g2, nw.im[c], yv.im[c]);
+                    yo.re[c] = add_terms(a.y_terms, g0, o.re[c], g1, up.re[c], g2, nw.re[c], yv.re[c]);
+                    yo.im[c] = add_terms(a.y_terms, g0, o.im[c], g1, up.im[c], g2, nw.im[c], yv.im[c]);
                 }
             }
             if constexpr (mode_first(MODE)) {

@@ -10,14 +10,25 @@ namespace chebfd {
 // Variants of the fused step kernel.
 //  kModeFirst : N = (aH+bI) P                                 (Alg. 1, first product)
 //  kModeSecond: N = 2(aH+bI) P - O;  Y(=O) = g0 O + g1 P + g2 N   (Alg. 1, start of Y)
-//  kModeStep  : O = 2(aH+bI) P - O (in place);  Y += g2 O       (Alg. 1, recurrence step)
-//  kModeKpm   : O = 2(aH+bI) P - O (in place), no Y update      (moments only)
+//  kModeStep  : O' = 2(aH+bI) P - O (in place);  Y += [g0 O + [g1 P]] + g2 O'
+//               (Alg. 1, recurrence step; y_terms of the three products, last ones first)
+//  kModeKpm   : O = 2(aH+bI) P - O (in place), no Y update      (moments only, and the
+//               recurrence steps whose term a later kModeStep adds)
+// A recurrence step holds T_{p-2} x (old O), T_{p-1} x (P) and T_p x (new O) of its
+// row, so Y takes the terms of kYTerms = 3 steps at once: the filter runs two
+// kModeKpm steps and one kModeStep with y_terms = 3, in the order g_{p-2},
+// g_{p-1}, g_p (the same fused multiply-adds in the same order as one update per
+// step: bitwise equal results), and the block Y moves through HBM in every third
+// step only: 3 + 2/3 block rows per step instead of 5.  Measured per step, one
+// update per step -> per three: 64x64x32 FP64 n_b = 32 281 -> 231 us, n_b = 16
+// 165 -> 141 us, c64 n_b = 64 281 -> 243 us; 128x64x64 FP64 n_b = 32 1168 -> 952 us.
 // These four also form the per-column products <new, P> and <P, P>.  The
 // unfused filter (the SpMMV call of Alg. 1 on its own, followed by separate
 // dot and axpy calls) uses two more, which form no dot products:
 //  kModeSpmv   : N = (aH+bI) P
 //  kModeSpmvRec: O = 2(aH+bI) P - O (in place)
 enum { kModeFirst = 0, kModeSecond = 1, kModeStep = 2, kModeKpm = 3, kModeSpmv = 4, kModeSpmvRec = 5 };
+constexpr int kYTerms = 3;
 constexpr bool mode_dots(int mode) { return mode <= kModeKpm; }
 constexpr bool mode_first(int mode) { return mode == kModeFirst || mode == kModeSpmv; }
 
@@ -37,6 +48,7 @@ struct StepArgs {
     void *Y;                    // filtered block
     double alpha, beta;
     double g0, g1, g2;
+    int32_t y_terms;            // kModeStep: terms added to Y (1: g2 O', 2: g1 P too, 3: g0 O too)
     double *part_out;           // [3*NB][G] partial dot products of this launch
     const double *part_in;      // [3*NB][G_prev] partials of the previous launch, or null
     double *red_eta;            // destination of the reduced eta (re, im pairs) [NB]

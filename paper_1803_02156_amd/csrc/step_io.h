@@ -82,5 +82,17 @@ __device__ inline void store_pack_nt(T *p, const Pack<T, CPL> &r) {
     }
 }
 
+// One component of Y + g0 o + g1 u + g2 w, its last `terms` products only (the
+// same in every lane: a select on a scalar, no branch that would split the
+// instruction stream between the loads and their wait).
+template <typename T>
+__device__ inline T add_terms(int terms, T g0, T o, T g1, T u, T g2, T w, T y) {
+    const T y0 = fma(g0, o, y);
+    y = terms > 2 ? y0 : y;
+    const T y1 = fma(g1, u, y);
+    y = terms > 1 ? y1 : y;
+    return fma(g2, w, y);
+}
+
 }  // namespace step_io
 }  // namespace chebfd
