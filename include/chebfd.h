@@ -173,9 +173,12 @@ int chebfd_random_phase(const chebfd_matrix *H, int32_t m, int32_t n_b, int32_t 
  * (with <a, b> = sum_i conj(a_i) b_i, FP64 accumulation, deterministic
  * summation order); row 0 is not written.  May be NULL together (moments not
  * needed is not faster: they are computed in the same pass).
- * d_work: chebfd_filter_query bytes (the partial sums of the dot products and
+ * d_work: chebfd_filter_query bytes (the partial sums of the dot products,
  * one progress word per workgroup of the window kernel, tagged per launch, so
- * nothing has to start at zero).  n_b in {1,2,4,8,16,32,64,128},
+ * nothing has to start at zero, and for small matrices the U and W blocks of up
+ * to 7 further blocks of the search space, at most 16 MB with their partial sums
+ * beside them, which are then stepped by one launch; the results do not depend on
+ * it).  n_b in {1,2,4,8,16,32,64,128},
  * n_s % n_b == 0, n_p >= 0, gamma[n_p + 1] on the host.
  * Buffers must be 256-byte aligned and must not overlap.
  */
@@ -193,7 +196,9 @@ int chebfd_filter_query(const chebfd_matrix *H, int32_t n_b, size_t *work_bytes)
  *                          ranges of one XCD are held within a few tiles of
  *                          each other through progress words in the workspace
  *   CHEBFD_KERNEL_LDS      the tile's matrix slots staged in LDS, U gathered from
- *                          memory (rows of up to 16 entries, C <= 32)
+ *                          memory (rows of up to 16 entries, C <= 32; small
+ *                          matrices by a variant in which each wavefront stages
+ *                          its own rows' slots)
  *   CHEBFD_KERNEL_ROW      one row per wavefront group (n_b >= 32, wider rows)
  *   CHEBFD_KERNEL_MULTIROW several rows per wavefront (n_b < 32, wider rows)
  */

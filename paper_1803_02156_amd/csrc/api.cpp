@@ -487,7 +487,9 @@ struct StepGeometry {
     int kind;           // 0 = LDS-staged, 1 = row per wavefront, 2 = multi-row, 3 = window
     int64_t npass;      // passes (kinds 1, 2)
     int G;
+    bool wave;          // kind 0: the small-matrix variant (a wavefront stages its own rows)
     LdsGeometry lds;
+    WaveGeometry small;
     WinGeometry win;
 };
 
@@ -495,14 +497,16 @@ static int filter_geometry(const chebfd_matrix *H, int prec, int nb, StepGeometr
     DeviceProps d;
     int rc = device_props(&d);
     if (rc) return rc;
+    g->wave = false;
     if (win_geometry(H, prec, nb, d.num_cus, &g->win)) {
         g->kind = 3;
         g->npass = g->win.ntiles;
         g->G = g->win.G;
     } else if (lds_geometry(H, prec, nb, d.num_cus, &g->lds)) {
         g->kind = 0;
-        g->npass = g->lds.ntiles;
-        g->G = g->lds.G;
+        g->wave = wave_geometry(H, prec, nb, &g->small);
+        g->npass = g->wave ? g->small.npass : g->lds.ntiles;
+        g->G = g->wave ? g->small.G : g->lds.G;
     } else if (nb >= kRowKernelMinNb) {
         g->kind = 1;
         const int rows = row_kernel_rows_per_pass(nb);
@@ -520,10 +524,31 @@ static int filter_geometry(const chebfd_matrix *H, int prec, int nb, StepGeometr
     return CHEBFD_OK;
 }
 
+// Small matrices: further workspace that lets one launch step up to small.batch
+// blocks of the search space (the U and W of all but the first and the partial sums
+// of all), after the part that one block needs.  A workspace without it is taken too, block by block.
+struct BatchLayout {
+    size_t part, u, w, total;   // offsets of the second partial buffer, U and W
+};
+static BatchLayout batch_layout(const chebfd_matrix *H, int prec, int nb, const StepGeometry &g) {
+    BatchLayout L{0, 0, 0, 0};
+    if (!g.wave || g.small.batch < 2) return L;
+    const size_t k = g.small.batch, blocks = round_up((k - 1) * vec_elem_bytes(prec) * (size_t)H->n * nb, 256);
+    L.part = filter_part_bytes(nb, g.G * g.small.batch);
+    L.u = 2 * L.part;
+    L.w = L.u + blocks;
+    L.total = L.w + blocks;
+    return L;
+}
+static size_t batch_bytes(const chebfd_matrix *H, int prec, int nb, const StepGeometry &g) {
+    return batch_layout(H, prec, nb, g).total;
+}
+
 static int launch_any(const chebfd_matrix *H, int prec, int nb, int mode, StepArgs a,
                       const StepGeometry &g, hipStream_t s) {
     a.npass = g.npass;
     if (g.kind == 3) return launch_win_step(prec, nb, mode, a, g.win, s);
+    if (g.wave) return launch_wave_step(prec, nb, mode, a, g.small, s);
     if (g.kind == 0) return launch_lds_step(prec, nb, mode, a, g.lds, s);
     if (g.kind == 1) return launch_row_step(prec, nb, H->max_width, mode, a, g.G, s);
     return launch_step(prec, nb, mode, a, g.G, s);
@@ -536,7 +561,7 @@ int chebfd_filter_query(const chebfd_matrix *H, int32_t n_b, size_t *work_bytes)
     CHEBFD_REQUIRE(work_bytes != nullptr, "work_bytes is NULL");
     StepGeometry g;
     if ((rc = filter_geometry(H, H->prec, n_b, &g))) return rc;
-    *work_bytes = filter_work_bytes(n_b, g.G);
+    *work_bytes = filter_work_bytes(n_b, g.G) + batch_bytes(H, H->prec, n_b, g);
     return CHEBFD_OK;
 }
 
@@ -565,12 +590,13 @@ static StepArgs base_args(const chebfd_matrix *H, double alpha, double beta) {
     a.alpha = alpha;
     a.beta = beta;
     a.uniform_width = H->uniform_width;
+    a.batch = 1;
     return a;
 }
 
 static int filter_run(const chebfd_matrix *H, double alpha, double beta, const double *h_gamma, int n_p,
                       int n_s, int n_b, int prec, void *d_xy, void *d_u, void *d_w, double *d_eta,
-                      double *d_nu, void *d_work, size_t need, const StepGeometry &geo, bool moments_only,
+                      double *d_nu, void *d_work, size_t work_bytes, const StepGeometry &geo, bool moments_only,
                       hipStream_t s);
 
 // Argument checks shared by chebfd_filter and chebfd_filter_unfused; on
@@ -606,7 +632,14 @@ static int check_filter_args(const chebfd_matrix *H, double alpha, double beta, 
         const size_t mb = sizeof(double) * (size_t)(n_p + 1) * n_s;
         CHEBFD_REQUIRE(!overlap(d_eta, 2 * mb, d_nu, mb), "d_eta and d_nu overlap");
     }
-    *need_out = need;
+    // several blocks per launch where the workspace has room for them beside everything else
+    const size_t more = n_s > n_b ? batch_bytes(H, prec, n_b, *geo) : 0;
+    const size_t mom = sizeof(double) * (size_t)(n_p + 1) * n_s;
+    const bool room = more > 0 && work_bytes >= need + more && !overlap(d_work, need + more, d_xy, xy_bytes) &&
+                      !overlap(d_work, need + more, d_u, blk) && !overlap(d_work, need + more, d_w, blk) &&
+                      (!d_eta || (!overlap(d_work, need + more, d_eta, 2 * mom) &&
+                                  !overlap(d_work, need + more, d_nu, mom)));
+    *need_out = room ? need + more : need;
     return CHEBFD_OK;
 }
 
@@ -740,7 +773,7 @@ static int filter_unfused_run(const chebfd_matrix *H, double alpha, double beta,
 // update (the KPM moments); X is then overwritten by Chebyshev vectors.
 static int filter_run(const chebfd_matrix *H, double alpha, double beta, const double *h_gamma, int n_p,
                       int n_s, int n_b, int prec, void *d_xy, void *d_u, void *d_w, double *d_eta,
-                      double *d_nu, void *d_work, size_t need, const StepGeometry &geo, bool moments_only,
+                      double *d_nu, void *d_work, size_t work_bytes, const StepGeometry &geo, bool moments_only,
                       hipStream_t s) {
     int rc;
     const int G = geo.G;
@@ -749,16 +782,41 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
     part[0] = static_cast<double *>(d_work);
     part[1] = reinterpret_cast<double *>(static_cast<char *>(d_work) + filter_part_bytes(n_b, G));
     int64_t *prog = filter_prog(d_work, n_b, G);
-    (void)need;
     const int nblocks = n_s / n_b;
     const int64_t count = H->n * (int64_t)n_b;
+    // blocks that one launch steps: more than one for small matrices, when there
+    // are more and the workspace has room for their U and W
+    int batch = 1;
+    char *more_u = nullptr, *more_w = nullptr;
+    const BatchLayout bl = batch_layout(H, prec, n_b, geo);
+    if (bl.total > 0 && nblocks > 1 && work_bytes >= filter_work_bytes(n_b, G) + bl.total) {
+        batch = geo.small.batch;
+        char *base = static_cast<char *>(d_work) + filter_work_bytes(n_b, G);
+        part[0] = reinterpret_cast<double *>(base);
+        part[1] = reinterpret_cast<double *>(base + bl.part);
+        more_u = base + bl.u;
+        more_w = base + bl.w;
+    }
+    // the batch's blocks after the first, for the first block's address
+    auto more = [&](const void *first) -> void * {
+        if (first == nullptr || batch == 1) return nullptr;
+        if (first == d_u) return more_u;
+        if (first == d_w) return more_w;
+        return static_cast<char *>(const_cast<void *>(first)) + blk;   // consecutive in d_xy
+    };
 
     // pending reduction: the partials of the last launch and where they go
     const double *pend_part = nullptr;
     double *pend_eta = nullptr, *pend_nu = nullptr;
     int flip = 0;
+    int kb = 1;   // blocks of the current batch
     auto next_args = [&](StepArgs a, int p, int b) {
-        a.part_out = part[flip];
+        a.batch = kb;
+        a.P1 = more(a.P);
+        a.O1 = more(a.O);
+        a.N1 = more(a.N);
+        a.Y1 = more(a.Y);
+        a.part_out = d_eta ? part[flip] : nullptr;   // null: the dot products are not wanted
         a.part_in = pend_part;
         a.red_eta = pend_eta;
         a.red_nu = pend_nu;
@@ -778,12 +836,29 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
         return a;
     };
 
-    for (int b = 0; b < nblocks; ++b) {
+    // the sums of the last launch
+    auto flush = [&]() -> int {
+        if (!d_eta || !pend_part) return CHEBFD_OK;
+        StepArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.part_in = pend_part;
+        a.red_eta = pend_eta;
+        a.red_nu = pend_nu;
+        a.G_prev = G;
+        a.batch = kb;
+        pend_part = nullptr;
+        return geo.wave ? launch_wave_reduce(n_b, a, s) : launch_reduce(n_b, a, s);
+    };
+
+    for (int b = 0; b < nblocks; b += kb) {
+        // a launch sums the previous launch's partials of as many blocks as it steps
+        if (std::min(batch, nblocks - b) != kb && (rc = flush())) return rc;
+        kb = std::min(batch, nblocks - b);
         char *X = static_cast<char *>(d_xy) + blk * b;
         void *A = d_u, *B = d_w;
         if (n_p == 0) {
             if (!moments_only &&
-                (rc = launch_axpby_blocked(prec, count, h_gamma[0], X, 0.0, nullptr, s)))
+                (rc = launch_axpby_blocked(prec, count * kb, h_gamma[0], X, 0.0, nullptr, s)))
                 return rc;
             continue;
         }
@@ -806,6 +881,9 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
         }
         if (n_p == 1) {
             if ((rc = launch_axpby_blocked(prec, count, h_gamma[0], X, h_gamma[1], A, s))) return rc;
+            if (kb > 1 &&
+                (rc = launch_axpby_blocked(prec, count * (kb - 1), h_gamma[0], X + blk, h_gamma[1], more(A), s)))
+                return rc;
             continue;
         }
         // W <- 2(aH + bI) U - X;  X <- g0c0 X + g1c1 U + g2c2 W         (Alg. 1, start of Y)
@@ -838,16 +916,7 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
             std::swap(Ub, Wb);
         }
     }
-    if (d_eta && pend_part) {
-        StepArgs a;
-        std::memset(&a, 0, sizeof(a));
-        a.part_in = pend_part;
-        a.red_eta = pend_eta;
-        a.red_nu = pend_nu;
-        a.G_prev = G;
-        if ((rc = launch_reduce(n_b, a, s))) return rc;
-    }
-    return CHEBFD_OK;
+    return flush();
 }
 
 // KPM workspace: X (R vectors, blocked by n_b = min(R, 32)), U, eta, nu and the
@@ -864,7 +933,7 @@ static int kpm_layout(const chebfd_matrix *H, int n_steps, int R, StepGeometry *
                    "R = %d must be a power of two up to 32 or a multiple of 32", R);
     const int n_b = R < 32 ? R : 32;
     if ((rc = filter_geometry(H, H->prec, n_b, geo))) return rc;
-    L->filter_bytes = filter_work_bytes(n_b, geo->G);
+    L->filter_bytes = filter_work_bytes(n_b, geo->G) + (R > n_b ? batch_bytes(H, H->prec, n_b, *geo) : 0);
     const size_t sw = vec_elem_bytes(H->prec), n = H->n;
     size_t at = 0;
     auto take = [&](size_t b) { size_t h = at; at = round_up(at + b, 256); return h; };

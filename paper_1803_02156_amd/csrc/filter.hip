@@ -185,6 +185,7 @@ __global__ __launch_bounds__(kThreads) void cheb_step_kernel(StepArgs a) {
         }
     }
     if constexpr (!mode_dots(MODE)) return;
+    if (a.part_out == nullptr) return;
 
     // workgroup reduction over the ROWS lanes of each column, fixed order
     sred[tid] = e_re;

@@ -313,6 +313,7 @@ __global__ __launch_bounds__(kThreads) void cheb_lds_kernel(StepArgs a, int tile
     }
 
     if constexpr (!mode_dots(MODE)) return;
+    if (a.part_out == nullptr) return;
     // workgroup reduction over the ROWS lanes of each column, fixed order;
     // sred[(component * CPL + c) * kThreads + lane]
 #pragma unroll

@@ -220,6 +220,7 @@ __global__ __launch_bounds__(kThreads) void cheb_row_kernel(StepArgs a) {
         }
     }
     if constexpr (!mode_dots(MODE)) return;
+    if (a.part_out == nullptr) return;
 
     // workgroup reduction in a fixed order: the two halves, then the rows of
     // the pass that share this column block

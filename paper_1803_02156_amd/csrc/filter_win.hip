@@ -426,6 +426,7 @@ __global__ __launch_bounds__(kWinThreads) void cheb_win_kernel(StepArgs a, int64
         __hip_atomic_store(my_prog, tag | static_cast<uint32_t>(te - tb), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     if constexpr (!mode_dots(MODE)) return;
+    if (a.part_out == nullptr) return;
     // workgroup reduction over the TR lanes of each column, fixed order;
     // sred[(component * CPL + c) * kWinThreads + lane] (over the ring: every
     // wave has passed the last barrier of the tile loop)

@@ -49,11 +49,14 @@ struct StepArgs {
     double alpha, beta;
     double g0, g1, g2;
     int32_t y_terms;            // kModeStep: terms added to Y (1: g2 O', 2: g1 P too, 3: g0 O too)
-    double *part_out;           // [3*NB][G] partial dot products of this launch
+    double *part_out;           // [3*NB][G] partial dot products of this launch, or null (not wanted)
     const double *part_in;      // [3*NB][G_prev] partials of the previous launch, or null
     double *red_eta;            // destination of the reduced eta (re, im pairs) [NB]
     double *red_nu;             // destination of the reduced nu [NB]
     int32_t G_prev;
+    int32_t batch;              // blocks per launch (small-matrix kernel): the first in P, O, N and Y,
+    const void *P1;             // the others one after another from here on
+    void *O1, *N1, *Y1;
     int32_t uniform_width;      // every chunk has this many slots per row (0: read chunk_width)
     int64_t *prog;              // [G] progress words of the window kernel's lead control, or null
     int32_t epoch;              // this launch's tag in prog (nonzero, distinct from recent launches)
@@ -75,6 +78,34 @@ struct LdsGeometry {
 bool lds_geometry(const chebfd_matrix *H, int prec, int nb, int num_cus, LdsGeometry *g);
 int launch_lds_step(int prec, int nb, int mode, const StepArgs &a, const LdsGeometry &g,
                     hipStream_t s);
+// Step kernel for small matrices (filter_wave.hip): each wavefront stages its
+// own rows' matrix slots, one pass per workgroup
+constexpr int kWaveMaxWidth = 16;   // rows of at most this many stored entries
+// U, W and Y together at most this: past it they leave the 256 MB memory-side
+// cache and the LDS-staged kernel's non-temporal streams win (FP64, measured per
+// step, LDS-staged against this kernel: 131072 rows n_b = 32, 201 MB, 74 and 64 us;
+// 294912 rows n_b = 16, 226 MB, 77 and 81; 98304 rows n_b = 64, 302 MB, 108 and
+// 133).  n_b = 1 takes this kernel at every size (294912 rows 26 and
+// 16 us, 2097152 rows 150 and 130).
+constexpr int64_t kWaveMaxBytes = 210000000;
+// At most four workgroups per CU: further ones only add partial sums (36864 rows,
+// c64 n_b = 32: 10.9 us with 1024, 12.1 with 2048); n_b = 128 half of that, which
+// keeps the partial sums of one block within 4 MB.
+constexpr int kWaveMaxGrid = 1024;
+constexpr int kWaveMaxPartials = 65536;   // workgroups times n_b
+// Blocks per launch: until about two passes for every workgroup (8192 rows FP64,
+// 1024 passes per block: one block 7.8 us, the work of two 9.3, of four 17)
+constexpr int kWaveBatchPasses = 2048;
+constexpr int kWaveMaxBatch = 8;
+struct WaveGeometry {
+    int maxw;           // compile-time row width of the kernel instance (13 or 16)
+    int G;              // workgroups that step (the reduction adds its own)
+    int64_t npass;      // row passes
+    int batch;          // blocks of n_b vectors that one launch steps, at most
+};
+bool wave_geometry(const chebfd_matrix *H, int prec, int nb, WaveGeometry *g);
+int launch_wave_step(int prec, int nb, int mode, const StepArgs &a, const WaveGeometry &g, hipStream_t s);
+int launch_wave_reduce(int nb, const StepArgs &a, hipStream_t s);
 // Window step kernel (filter_win.hip): one 1024-thread workgroup per CU sweeps
 // a contiguous range of tiles and gathers from a ring of U rows staged in LDS
 // (kWinBlocks blocks of one tile each; tile t reads blocks t - h .. t + h,

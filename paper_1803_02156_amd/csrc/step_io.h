@@ -82,6 +82,21 @@ __device__ inline void store_pack_nt(T *p, const Pack<T, CPL> &r) {
     }
 }
 
+template <typename T, int CPL>
+__device__ inline void store_pack(T *p, const Pack<T, CPL> &r) {
+    if constexpr (CPL == 2) {
+        fv4 v;
+        v.x = r.re[0];
+        v.y = r.im[0];
+        v.z = r.re[1];
+        v.w = r.im[1];
+        *reinterpret_cast<fv4 *>(p) = v;
+    } else {
+        using VT = typename V2<T>::type;
+        *reinterpret_cast<VT *>(p) = VT{r.re[0], r.im[0]};
+    }
+}
+
 // One component of Y + g0 o + g1 u + g2 w, its last `terms` products only (the
 // same in every lane: a select on a scalar, no branch that would split the
 // instruction stream between the loads and their wait).
