@@ -30,6 +30,20 @@ typedef double d4v __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 256;
 
+// Keeps MFMA accumulators in accumulation registers across a loop's back edge:
+// left alone the compiler carries them in vector registers in some instances and
+// moves all of them there and back in every stage (128 moves per 64 products, and
+// two waves per SIMD instead of three: update 524288 x 256 x 256 c64 4677 -> 4321 us).
+template <int NY>
+__device__ inline void hold_acc(d4v (&acc)[2][NY][2]) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < NY; ++y)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) asm volatile("" : "+a"(acc[x][y][q]));
+}
+
 __device__ inline double2 load_c(const void *base, int prec, int64_t idx) {
     if (prec == CHEBFD_PREC_FP64) return static_cast<const double2 *>(base)[idx];
     const float2 f = static_cast<const float2 *>(base)[idx];
@@ -60,25 +74,33 @@ __device__ inline int64_t blocked_index(int64_t n, int nb, int64_t i, int c) {
 // Gram: S(a, b) = sum_i conj(A(i, a)) B(i, b), 64 x 64 complex output tile per
 // workgroup (4 waves, 32 x 32 each = 2 x 2 MFMA tiles x 4 real products), rows
 // [r0, r1) of one split; partial tiles go to part[split][tile] and are summed
-// in split order by gram_reduce_kernel.  For the Hermitian product A^H A only
-// the tiles on and above the diagonal are formed (tile index t enumerates them
-// column by column) and the reduction mirrors them.
+// in a fixed order by gram_reduce_kernel.  For the Hermitian product A^H A only
+// the tiles on and above the diagonal are formed, by a launch of their own (DIAG)
+// for those on it: each of these needs ten of its sixteen 16 x 16 products and
+// one operand (at most 32 columns: three products, the rows quartered among the
+// waves).  The reduction mirrors them.  Waves skip products of columns past the
+// matrices.  Bound: FP64 matrix cores (a plain FP64 product of 8192^2 reaches 71
+// TFLOP/s here).  Time of A^H A, every tile whole and 4096 tile-splits -> now:
+// 524288 x 256 c64 2674 -> 2330 us, x 128 c128 1229 -> 698, x 32 c64 515 -> 81;
+// 8192 x 32 c128 55 -> 17; 524288 x 256 x 32 c64 (BW = 32) 963 -> 588.
 // ---------------------------------------------------------------------------
 constexpr int kGT = 64;   // output tile edge
 constexpr int kGK = 16;   // rows per LDS stage
+constexpr int kGramPerCu = 3;   // resident workgroups per CU (registers); one more of the BW = 32 instances
+constexpr int kGramRounds = 2;
 
-// (row tile, column tile) of output tile t: column-major over all tiles, or
-// over the upper triangle (row tile <= column tile) when herm
+// (row tile, column tile) of output tile t.  General product: column-major over all
+// tiles.  Hermitian product: the tiles above the diagonal, column by column.
 __device__ inline void gram_tile(int t, int tiles_a, bool herm, int *ta, int *tb) {
     if (!herm) {
         *ta = t % tiles_a;
         *tb = t / tiles_a;
         return;
     }
-    int c = 0;
-    while ((c + 1) * (c + 2) / 2 <= t) ++c;
+    int c = 1;
+    while (c * (c + 1) / 2 <= t) ++c;
     *tb = c;
-    *ta = t - c * (c + 1) / 2;
+    *ta = t - c * (c - 1) / 2;
 }
 
 // Element types TA, TB of A and B (double: c128, float: c64) are template
@@ -86,10 +108,10 @@ __device__ inline void gram_tile(int t, int tiles_a, bool herm, int *ta, int *tb
 // a branch and kept the prefetch registers FP64 wide (two waves per SIMD
 // instead of three; 287 -> 162 ms for a 33.5 M x 256 c64 product).  Stages stay
 // in registers in the storage type until they go to LDS as FP64.
-template <typename TA, typename TB, int BW>
+template <typename TA, typename TB, int BW, bool DIAG>
 __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const void *B, int nb_b, int64_t n,
                                                    int m1, int m2, int tiles_a, int herm, int64_t rows_per_split,
-                                                   double *part) {
+                                                   int ntiles, int nsplit, double *part) {
     // output tile 64 (columns of A) x BW (columns of B); BW = 32 for products of at
     // most 32 columns of B (Rayleigh-Ritz and TSQR panels), so no wave multiplies zeros
     constexpr int KG = kGK;
@@ -97,11 +119,19 @@ __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const
     using RA = typename std::conditional<std::is_same<TA, double>::value, double2, float2>::type;
     using RB = typename std::conditional<std::is_same<TB, double>::value, double2, float2>::type;
     __shared__ double2 sa[KG][kGT];
-    __shared__ double2 sb[KG][BW];
-    const int tile = blockIdx.x;
-    const int split = blockIdx.y;
-    int ta, tb;
-    gram_tile(tile, tiles_a, herm != 0, &ta, &tb);
+    __shared__ double2 sb[DIAG ? 1 : KG][BW];
+    // all tiles of a split on one XCD (workgroup w runs on XCD w % 8): they read the same rows
+    int tile, split;
+    if (nsplit % 8 == 0) {
+        const int k = blockIdx.x / 8;
+        tile = k % ntiles;
+        split = k / ntiles * 8 + blockIdx.x % 8;
+    } else {
+        tile = blockIdx.x % ntiles;
+        split = blockIdx.x / ntiles;
+    }
+    int ta = tile, tb = tile;
+    if constexpr (!DIAG) gram_tile(tile, tiles_a, herm != 0, &ta, &tb);
     const int a0 = ta * kGT, b0 = tb * BW;
     const int64_t r0 = (int64_t)split * rows_per_split;
     const int64_t r1 = r0 + rows_per_split < n ? r0 + rows_per_split : n;
@@ -109,6 +139,22 @@ __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int wa = (wv & 1) * 32, wb = (wv >> 1) * (BW / 2);  // wave's 32 x BW/2 sub-tile
+    // whether the wave's products, and those of its second 16 columns of B, reach into the matrices
+    const bool live = __builtin_amdgcn_readfirstlane(a0 + wa < m1 && b0 + wb < m2);
+    const bool both = __builtin_amdgcn_readfirstlane(b0 + wb + 16 < m2);
+    // DIAG: products (row, column) in units of 16: role 0 (0,0) (0,1) (1,1), role 1
+    // (0,2) (0,3) (1,3), role 2 (1,2) (2,2), role 3 (2,3) (3,3); the roles of three
+    // products alternate between the wave pairs (that is, between SIMDs)
+    const int role = __builtin_amdgcn_readfirstlane((wv + 2 * (split & 1)) & 3);
+    const bool quarter = DIAG && m1 <= 32;   // one tile of at most 2 x 2 products
+    const int part_of = quarter ? 0 : role;
+    const int np = part_of < 2 ? 3 : 2;
+    int ro[3], co[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        ro[p] = 16 * (p == 2 ? 1 : part_of < 2 ? 0 : part_of - 1 + p);
+        co[p] = 16 * (p == 2 ? 1 + 2 * part_of : part_of == 0 ? p : part_of == 1 ? 2 + p : part_of);
+    }
 
     // two accumulators per 16 x 16 tile: real and imaginary part of the sum
     d4v acc[2][NY][2];
@@ -122,9 +168,9 @@ __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const
     // Stages of KG rows x 64 columns of A and KG rows x BW columns of B (zero
     // outside the matrices): the next stage's global loads are issued before the
     // current stage's products, so their latency hides behind the matrix-core work.
-    constexpr int kPerA = KG * kGT / kT, kPerB = KG * BW / kT;   // elements per thread
+    constexpr int kPerA = KG * kGT / kT, kPerB = DIAG ? 0 : KG * BW / kT;   // elements per thread
     RA ra[kPerA];
-    RB rb2[kPerB];
+    RB rb2[kPerB > 0 ? kPerB : 1];
     auto fetch = [&](int64_t rbase) {
 #pragma unroll
         for (int q = 0; q < kPerA; ++q) {
@@ -146,6 +192,7 @@ __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const
         }
     };
     if (r0 < r1) fetch(r0);
+    hold_acc<NY>(acc);
     for (int64_t rb = r0; rb < r1; rb += KG) {
 #pragma unroll
         for (int q = 0; q < kPerA; ++q) {
@@ -159,68 +206,140 @@ __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const
         }
         __syncthreads();
         if (rb + KG < r1) fetch(rb + KG);
+        // conj(a) b = (ar br + ai bi) + i (ar bi - ai br)
+        auto product = [&](const double2 av, const double2 bv, d4v *c) {
+            c[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.x, c[0], 0, 0, 0);
+            c[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, bv.y, c[0], 0, 0, 0);
+            c[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.y, c[1], 0, 0, 0);
+            c[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av.y, bv.x, c[1], 0, 0, 0);
+        };
+        if constexpr (DIAG) {
+            // at most 32 columns: every wave takes role 0 for a quarter of the rows
 #pragma unroll
-        for (int k0 = 0; k0 < KG; k0 += 4) {
-            const int kk = k0 + lane / 16;
+            for (int k0 = 0; k0 < KG; k0 += 4) {
+                if (quarter && k0 != 4 * role) continue;
+                const int kk = k0 + lane / 16;
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const double2 av = sa[kk][wa + 16 * x + lane % 16];
+                for (int p = 0; p < 2; ++p)
+                    product(sa[kk][ro[p] + lane % 16], sa[kk][co[p] + lane % 16], acc[0][p % NY]);
+                if (np > 2) product(sa[kk][ro[2] + lane % 16], sa[kk][co[2] + lane % 16], acc[1][0]);
+            }
+        } else if (live) {
+#pragma unroll
+            for (int k0 = 0; k0 < KG; k0 += 4) {
+                const int kk = k0 + lane / 16;
+                double2 av[2];
+#pragma unroll
+                for (int x = 0; x < 2; ++x) av[x] = sa[kk][wa + 16 * x + lane % 16];
 #pragma unroll
                 for (int y = 0; y < NY; ++y) {
+                    if (y > 0 && !both) continue;
                     const double2 bv = sb[kk][wb + 16 * y + lane % 16];
-                    // conj(a) b = (ar br + ai bi) + i (ar bi - ai br)
-                    acc[x][y][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.x, acc[x][y][0], 0, 0, 0);
-                    acc[x][y][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, bv.y, acc[x][y][0], 0, 0, 0);
-                    acc[x][y][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.y, acc[x][y][1], 0, 0, 0);
-                    acc[x][y][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av.y, bv.x, acc[x][y][1], 0, 0, 0);
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) product(av[x], bv, acc[x][y]);
                 }
             }
         }
+        hold_acc<NY>(acc);
         __syncthreads();
+    }
+    if constexpr (DIAG) {
+        if (quarter) {
+            // the four quarters' sums, in order, through the (idle) stage buffer
+            double2 *sw = &sa[0][0];
+            for (int v = 1; v < 4; ++v) {
+                if (role == v) {
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) sw[(p * 4 + r) * 64 + lane] = double2{acc[p / 2][p % 2][0][r], acc[p / 2][p % 2][1][r]};
+                }
+                __syncthreads();
+                if (role == 0) {
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const double2 t = sw[(p * 4 + r) * 64 + lane];
+                            acc[p / 2][p % 2][0][r] += t.x;
+                            acc[p / 2][p % 2][1][r] += t.y;
+                        }
+                }
+                __syncthreads();
+            }
+            if (role != 0) return;
+        }
     }
     // write the partial tile into a 64 x 64 slot (column-major inside the slot;
     // a BW = 32 tile fills its first 32 columns, the reduction reads no others)
-    double2 *out = reinterpret_cast<double2 *>(part) +
-                   ((int64_t)split * gridDim.x + tile) * (kGT * kGT);
+    double2 *out = reinterpret_cast<double2 *>(part) + ((int64_t)split * ntiles + tile) * (kGT * kGT);
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int y = 0; y < NY; ++y)
+        for (int y = 0; y < NY; ++y) {
+            const int p = x * NY + y;
+            if (DIAG && p >= np) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int ra = wa + 16 * x + lane / 16 + 4 * r;  // row of S (column of A)
-                const int cb = wb + 16 * y + lane % 16;            // column of S within the tile
+                const int ra = (DIAG ? ro[p % 3] : wa + 16 * x) + lane / 16 + 4 * r;  // row of S (column of A)
+                const int cb = (DIAG ? co[p % 3] : wb + 16 * y) + lane % 16;            // column of S within the tile
                 double2 v;
                 v.x = acc[x][y][0][r];
                 v.y = acc[x][y][1][r];
                 out[(int64_t)cb * kGT + ra] = v;
             }
+        }
 }
 
-// S = sum over splits (in split order) of the partial tiles; S column-major, ld.
-// herm: tiles above the diagonal also give their mirror image S(b, a) = conj S(a, b).
-__global__ __launch_bounds__(kT) void gram_reduce_kernel(const double *part, int nsplit, int ntiles,
+// S = sum over splits of the partial tiles; S column-major, ld.  A workgroup sums
+// kRE neighbouring entries of a tile, each with kRS threads that take every
+// kRS-th split and are then added in order.  (One thread per entry, walking all
+// splits one after the other, left a product of few tiles with a few workgroups
+// and took longer than the product itself: 524288 x 64 x 32, 2 tiles, 1024
+// splits: 288 of the 424 us that the whole product took, now 179.)
+// Hermitian product: the tiles on the diagonal first (nsplit_d splits each), then
+// the ntiles - tiles_a above it; entries above the diagonal also give their mirror
+// image S(b, a) = conj S(a, b).
+constexpr int kRE = 32, kRS = kT / kRE;
+__global__ __launch_bounds__(kT) void gram_reduce_kernel(const double *part, int nsplit, int nsplit_d, int ntiles,
                                                          int tiles_a, int herm, int m1, int m2, double *S,
                                                          int ld) {
-    const int64_t total = (int64_t)ntiles * kGT * kGT;
+    __shared__ double2 sred[kRS][kRE];
     const double2 *p = reinterpret_cast<const double2 *>(part);
-    for (int64_t t = blockIdx.x * (int64_t)kT + threadIdx.x; t < total; t += (int64_t)gridDim.x * kT) {
-        const int tile = static_cast<int>(t / (kGT * kGT));
-        const int e = static_cast<int>(t % (kGT * kGT));
-        const int ra = e % kGT, cb = e / kGT;
-        int ta, tb;
-        gram_tile(tile, tiles_a, herm != 0, &ta, &tb);
-        const int a = ta * kGT + ra, b = tb * kGT + cb;
-        if (a >= m1 || b >= m2) continue;
-        double sr = 0.0, si = 0.0;
-        for (int s = 0; s < nsplit; ++s) {
-            const double2 v = p[((int64_t)s * ntiles + tile) * (kGT * kGT) + e];
-            sr += v.x;
-            si += v.y;
-        }
-        reinterpret_cast<double2 *>(S)[(int64_t)b * ld + a] = double2{sr, si};
-        if (herm && ta != tb) reinterpret_cast<double2 *>(S)[(int64_t)a * ld + b] = double2{sr, -si};
+    const int el = threadIdx.x % kRE, sl = threadIdx.x / kRE;
+    const int per_tile = gridDim.x / ntiles;   // workgroups per tile (its first columns, where it is narrow)
+    int tile = blockIdx.x / per_tile, set = ntiles, splits = nsplit;
+    const int e = blockIdx.x % per_tile * kRE + el;
+    int ta = tile, tb = tile;
+    if (!herm) {
+        gram_tile(tile, tiles_a, false, &ta, &tb);
+    } else if (tile < tiles_a) {
+        set = tiles_a;
+        splits = nsplit_d;
+    } else {
+        tile -= tiles_a;
+        set = ntiles - tiles_a;
+        p += (int64_t)nsplit_d * tiles_a * (kGT * kGT);
+        gram_tile(tile, tiles_a, true, &ta, &tb);
     }
+    double sr = 0.0, si = 0.0;
+#pragma unroll 8
+    for (int s = sl; s < splits; s += kRS) {
+        const double2 v = p[((int64_t)s * set + tile) * (kGT * kGT) + e];
+        sr += v.x;
+        si += v.y;
+    }
+    sred[sl][el] = double2{sr, si};
+    __syncthreads();
+    if (sl > 0) return;
+    for (int q = 1; q < kRS; ++q) {
+        sr += sred[q][el].x;
+        si += sred[q][el].y;
+    }
+    const int a = ta * kGT + e % kGT, b = tb * kGT + e / kGT;
+    if (a >= m1 || b >= m2 || (herm && a > b)) return;
+    reinterpret_cast<double2 *>(S)[(int64_t)b * ld + a] = double2{sr, si};
+    if (herm && a != b) reinterpret_cast<double2 *>(S)[(int64_t)a * ld + b] = double2{sr, -si};
 }
 
 // ---------------------------------------------------------------------------
@@ -247,6 +366,8 @@ __global__ __launch_bounds__(kT) void update_kernel(const void *A, int nb_a, con
     const int wv = threadIdx.x >> 6;
     const int wi = (wv & 1) * 32, wc = (wv >> 1) * (BW / 2);
     const double2 *Mc = reinterpret_cast<const double2 *>(M);
+    const bool live = __builtin_amdgcn_readfirstlane(c0 + wc < m2);
+    const bool both = __builtin_amdgcn_readfirstlane(c0 + wc + 16 < m2);
 
     // two accumulators per 16 x 16 tile: real and imaginary part of the sum
     d4v acc[2][NY][2];
@@ -282,6 +403,7 @@ __global__ __launch_bounds__(kT) void update_kernel(const void *A, int nb_a, con
         }
     };
     fetch(0);
+    hold_acc<NY>(acc);
     for (int k0 = 0; k0 < m1; k0 += kGK) {
 #pragma unroll
         for (int q = 0; q < kPerA; ++q) {
@@ -295,23 +417,30 @@ __global__ __launch_bounds__(kT) void update_kernel(const void *A, int nb_a, con
         }
         __syncthreads();
         if (k0 + kGK < m1) fetch(k0 + kGK);
+        // a m = (ar mr - ai mi) + i (ar mi + ai mr)
+        auto product = [&](const double2 av, const double2 mv, d4v *c) {
+            c[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, mv.x, c[0], 0, 0, 0);
+            c[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av.y, mv.y, c[0], 0, 0, 0);
+            c[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, mv.y, c[1], 0, 0, 0);
+            c[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, mv.x, c[1], 0, 0, 0);
+        };
+        if (live) {
 #pragma unroll
-        for (int kb = 0; kb < kGK; kb += 4) {
-            const int kk = kb + lane / 16;
+            for (int kb = 0; kb < kGK; kb += 4) {
+                const int kk = kb + lane / 16;
+                double2 av[2];
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const double2 av = sa[wi + 16 * x + lane % 16][kk];
+                for (int x = 0; x < 2; ++x) av[x] = sa[wi + 16 * x + lane % 16][kk];
 #pragma unroll
                 for (int y = 0; y < NY; ++y) {
+                    if (y > 0 && !both) continue;
                     const double2 mv = sm[kk][wc + 16 * y + lane % 16];
-                    // a m = (ar mr - ai mi) + i (ar mi + ai mr)
-                    acc[x][y][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, mv.x, acc[x][y][0], 0, 0, 0);
-                    acc[x][y][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av.y, mv.y, acc[x][y][0], 0, 0, 0);
-                    acc[x][y][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, mv.y, acc[x][y][1], 0, 0, 0);
-                    acc[x][y][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, mv.x, acc[x][y][1], 0, 0, 0);
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) product(av[x], mv, acc[x][y]);
                 }
             }
         }
+        hold_acc<NY>(acc);
         __syncthreads();
     }
 #pragma unroll
@@ -743,36 +872,66 @@ int launch_gram(const void *A, int prec_a, int nb_a, const void *B, int prec_b, 
     const int ta = (m1 + kGT - 1) / kGT, tb = (m2 + kGT - 1) / kGT;
     // A^H A: Hermitian, only the tiles on and above the diagonal
     const int herm = (A == B && prec_a == prec_b && nb_a == nb_b && m1 == m2) ? 1 : 0;
-    const int ntiles = herm ? ta * (ta + 1) / 2 : ta * tb;
-    const int64_t rps = ((n + nsplit - 1) / nsplit + 2 * kGK - 1) / (2 * kGK) * (2 * kGK);
-    const dim3 grid(ntiles, nsplit);
     const bool a64 = prec_a == CHEBFD_PREC_FP64, b64 = prec_b == CHEBFD_PREC_FP64;
     // at most 32 columns of B: 64 x 32 output tiles (the slots and the reduction stay 64 x 64)
     const bool narrow = !herm && m2 <= 32;
-#define CHEBFD_GRAM(TA_, TB_)                                                                              \
-    do {                                                                                                   \
-        if (narrow)                                                                                        \
-            hipLaunchKernelGGL((gram_kernel<TA_, TB_, 32>), grid, dim3(kT), 0, s, A, nb_a, B, nb_b, n, m1, \
-                               m2, ta, herm, rps, part);                                                   \
-        else                                                                                               \
-            hipLaunchKernelGGL((gram_kernel<TA_, TB_, 64>), grid, dim3(kT), 0, s, A, nb_a, B, nb_b, n, m1, \
-                               m2, ta, herm, rps, part);                                                   \
+    DeviceProps d;
+    int rc = device_props(&d);
+    if (rc) return rc;
+    // splits of a launch of `tiles` tiles: at most nsplit (the workspace), whole
+    // rounds of the resident workgroups where there is more than one (2560 workgroups
+    // for 768 places leave the last round a third full, and each split costs a 64 KB
+    // slot written and read; two and three rounds measure alike), a multiple of 8
+    // (one XCD per split)
+    auto splits = [&](int tiles, int per_cu) {
+        const int resident = per_cu * d.num_cus;
+        const int rounds = std::min<int64_t>(kGramRounds, (int64_t)tiles * nsplit / resident);
+        int k = rounds >= 1 ? std::max(1, rounds * resident / tiles) : nsplit;
+        if (k >= 8) k -= k % 8;
+        return k;
+    };
+    auto rows = [&](int k) { return ((n + k - 1) / k + kGK - 1) / kGK * kGK; };
+    const int ntiles = herm ? ta * (ta - 1) / 2 : ta * tb;      // of the general kernel
+    const int ks = ntiles > 0 ? splits(ntiles, narrow ? kGramPerCu + 1 : kGramPerCu) : 0;
+    const int kd = herm ? splits(ta, kGramPerCu) : 0;
+#define CHEBFD_GRAM_ONE(TA_, TB_, BW_, DIAG_, TILES_, K_, PART_)                                                 \
+    hipLaunchKernelGGL((gram_kernel<TA_, TB_, BW_, DIAG_>), dim3((TILES_) * (K_)), dim3(kT), 0, s, A, nb_a, B,   \
+                       nb_b, n, m1, m2, ta, herm, rows(K_), TILES_, K_, PART_)
+#define CHEBFD_GRAM(TA_, TB_)                                                     \
+    do {                                                                          \
+        if (narrow)                                                               \
+            CHEBFD_GRAM_ONE(TA_, TB_, 32, false, ntiles, ks, part);               \
+        else                                                                      \
+            CHEBFD_GRAM_ONE(TA_, TB_, 64, false, ntiles, ks, part);               \
     } while (0)
-    if (a64 && b64)
+    if (herm) {
+        if (a64)
+            CHEBFD_GRAM_ONE(double, double, 64, true, ta, kd, part);
+        else
+            CHEBFD_GRAM_ONE(float, float, 64, true, ta, kd, part);
+        CHEBFD_HIP(hipGetLastError());
+        double *above = part + (size_t)kd * ta * kGT * kGT * 2;
+        if (ntiles > 0) {
+            if (a64)
+                CHEBFD_GRAM_ONE(double, double, 64, false, ntiles, ks, above);
+            else
+                CHEBFD_GRAM_ONE(float, float, 64, false, ntiles, ks, above);
+        }
+    } else if (a64 && b64) {
         CHEBFD_GRAM(double, double);
-    else if (a64)
+    } else if (a64) {
         CHEBFD_GRAM(double, float);
-    else if (b64)
+    } else if (b64) {
         CHEBFD_GRAM(float, double);
-    else
+    } else {
         CHEBFD_GRAM(float, float);
+    }
 #undef CHEBFD_GRAM
+#undef CHEBFD_GRAM_ONE
     CHEBFD_HIP(hipGetLastError());
-    const int64_t total = (int64_t)ntiles * kGT * kGT;
-    int G = static_cast<int>((total + kT - 1) / kT);
-    if (G > 4096) G = 4096;
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(G), dim3(kT), 0, s, part, nsplit, ntiles, ta, herm, m1, m2,
-                       S, ld);
+    const int all = herm ? ta + ntiles : ntiles;
+    const int G = all * (kGT * (narrow ? 32 : kGT) / kRE);
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3(G), dim3(kT), 0, s, part, ks, kd, all, ta, herm, m1, m2, S, ld);
     CHEBFD_HIP(hipGetLastError());
     return CHEBFD_OK;
 }

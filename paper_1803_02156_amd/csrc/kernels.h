@@ -156,11 +156,12 @@ int launch_gram(const void *A, int prec_a, int nb_a, const void *B, int prec_b, 
 size_t gram_part_bytes(int m1, int m2, int nsplit);
 // Row splits of a Gram product S = A^H B (m1 x m2): enough workgroups for a few
 // full waves of the device (about 4096 64 x 64 tile-splits; the Hermitian
-// product forms about half of them) but at least 256 rows per split.
+// product forms about half of them) but at least 128 rows per split; launch_gram
+// takes fewer where that fills the device in whole rounds.
 inline int gram_splits(int64_t n, int m1, int m2) {
     const int64_t tiles = (int64_t)((m1 + 63) / 64) * ((m2 + 63) / 64);
     const int64_t want = (4096 + tiles - 1) / tiles;
-    const int64_t cap = n / 256 > 1 ? n / 256 : 1;
+    const int64_t cap = n / 128 > 1 ? n / 128 : 1;
     return static_cast<int>(want < 1024 ? (want < cap ? want : cap) : (1024 < cap ? 1024 : cap));
 }
 int launch_update(const void *A, int prec_a, int nb_a, const double *M, int ldm, void *Z, int prec_z,
