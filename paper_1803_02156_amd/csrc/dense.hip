@@ -490,7 +490,8 @@ constexpr int kJNormG = 64;    // workgroups of the norm reduction
 __device__ inline int rr_player(int m, int r, int k) {
     // round r, seat k of the circle method over players 0..m-1 (m even):
     // seat 0 holds player 0, the other seats rotate over 1..m-1
-    return k == 0 ? 0 : ((k - 1 + r) % (m - 1)) + 1;
+    const int x = k - 1 + r;   // r < m - 1, k < m
+    return k == 0 ? 0 : (x >= m - 1 ? x - (m - 1) : x) + 1;
 }
 
 struct JacobiRound {
@@ -595,6 +596,192 @@ __global__ __launch_bounds__(kJW) void jacobi_rows_kernel(int m, int me, int slo
     const int half = me / 2;
     for (int col = blockIdx.x; col < m; col += gridDim.x)
         for (int t = threadIdx.x; t < half; t += kJW) jacobi_row_rotate(Ac, lda, jr, slot, t, col, m);
+}
+
+// The same sweeps for a matrix that fits in the LDS of one CU with its eigenvectors
+// (m <= kJSmall), all of them in one launch of one workgroup.
+// Bound: the chain of a round (pair entries -> rotation -> barrier -> update ->
+// barrier), about 0.8 us at m = 32; a launch per round took about 6 us each with its
+// gap, plus a host synchronisation per sweep.  m = 32: about 1.1 ms -> 0.21 ms.  Larger
+// matrices (2 m (m + 1) entries in 160 KB of LDS) keep a launch per round.
+// With delta = d - a, h = sqrt(delta^2 + 4 |b|^2), r = |delta| + h the smaller rotation is
+// c = r g, s = 2 |b| g (sign of delta), g = 1 / sqrt(2 h r): one root and one inverse
+// root in a row instead of four roots and five divisions.  Columns are rotated as
+// (x, y) <- (c x - sigma y, conj(sigma) x + c y), sigma = s e^{-i phi}, which leaves out
+// the factor e^{-i phi} of the second column; a second wave keeps the product of
+// these factors per column, and the eigenvectors get it at the end, so they carry
+// the phases of the rotations above.  The matrix is scaled by a power of two.
+constexpr int kJSmall = 64;
+// |b|^2 at or below this (of a matrix with entries of order 1) is set to zero without a
+// rotation: nearer the smallest normal number c and sigma lose their digits, and with
+// equal diagonal entries the rotation would not be unitary
+constexpr double kJTiny2 = 1e-280;
+struct __align__(16) JacobiPair {
+    double c, sr, si;   // c, sigma
+    int p, q;
+};
+
+__device__ inline void jacobi_rotate(double c, double sr, double si, double2 &x, double2 &y) {
+    const double2 nx{c * x.x - (sr * y.x - si * y.y), c * x.y - (sr * y.y + si * y.x)};
+    const double2 ny{c * y.x + (sr * x.x + si * x.y), c * y.y + (sr * x.y - si * x.x)};
+    x = nx;
+    y = ny;
+}
+
+constexpr size_t jacobi_small_lds(int me) {
+    return (size_t)2 * me * (me + 1) * 16 + (size_t)(me / 2) * sizeof(JacobiPair) + (size_t)me * 16 +
+           16 * sizeof(double);
+}
+
+__global__ __launch_bounds__(1024) void jacobi_small_kernel(int m, int me, const double *A, int lda, double *V, int ldv,
+                                                            double *w, int max_sweeps, double tol, int *status) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int ld = me + 1;
+    double2 *sa = reinterpret_cast<double2 *>(smem);     // column c at sa + c ld
+    double2 *sv = sa + me * ld;
+    JacobiPair *pr = reinterpret_cast<JacobiPair *>(sv + me * ld);
+    double2 *ph = reinterpret_cast<double2 *>(pr + me / 2);   // left-out phase of every column
+    double *sred = reinterpret_cast<double *>(ph + me);
+    const int tid = threadIdx.x, nt = blockDim.x, half = me / 2;
+    const int lane = tid & 63, wv = tid >> 6, waves = nt >> 6;
+    const double2 *Ac = reinterpret_cast<const double2 *>(A);
+    double amax = 0.0;
+    for (int t = tid; t < me * me; t += nt) {
+        const int r = t % me, c = t / me;
+        const double2 v = r < m && c < m ? Ac[(int64_t)c * lda + r] : double2{0.0, 0.0};
+        sa[c * ld + r] = v;
+        sv[c * ld + r] = double2{r == c ? 1.0 : 0.0, 0.0};
+        amax = fmax(amax, fmax(fabs(v.x), fabs(v.y)));
+    }
+    for (int t = tid; t < me; t += nt) ph[t] = double2{1.0, 0.0};
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) amax = fmax(amax, __shfl_xor(amax, k));
+    if (lane == 0) sred[wv] = amax;
+    __syncthreads();
+    for (int k = 0; k < waves; ++k) amax = fmax(amax, sred[k]);
+    // a power of two brings the largest entry to [1, 2): no square over- or underflows
+    const int ex = amax > 0.0 && amax < INFINITY ? ilogb(amax) : 0;
+    for (int t = tid; t < me * me; t += nt) {
+        const int at = t / me * ld + t % me;
+        sa[at] = double2{ldexp(sa[at].x, -ex), ldexp(sa[at].y, -ex)};
+    }
+    __syncthreads();
+    // squared Frobenius norm, off-diagonal entries only if `off` (every thread gets it)
+    auto norm2 = [&](bool off) {
+        double acc = 0.0;
+        for (int t = tid; t < me * me; t += nt) {
+            const int r = t % me, c = t / me;
+            if (off && r == c) continue;
+            const double2 v = sa[c * ld + r];
+            acc += v.x * v.x + v.y * v.y;
+        }
+#pragma unroll
+        for (int k = 32; k >= 1; k >>= 1) acc += __shfl_xor(acc, k);
+        if (lane == 0) sred[wv] = acc;
+        __syncthreads();
+        acc = 0.0;
+        for (int k = 0; k < waves; ++k) acc += sred[k];
+        __syncthreads();
+        return acc;
+    };
+    // this thread's items of every round: 2 x 2 blocks of A (k1, k2), then pairs of V (row, k2)
+    constexpr int IT = (kJSmall / 2 * (kJSmall / 2) + kJSmall / 2 * kJSmall) / 1024;
+    const int nb2 = half * half, items = nb2 + half * me;
+    int i1[IT], i2[IT];
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+        const int t = tid + u * nt;
+        i1[u] = t < nb2 ? t % half : (t - nb2) % me;
+        i2[u] = t < nb2 ? t / half : (t - nb2) / me;
+    }
+    const double limit = tol * tol * norm2(false);
+    bool done = norm2(true) <= limit;
+    int sweep = 0;
+    for (; sweep < max_sweeps && !done; ++sweep) {
+        for (int r = 0; r < me - 1; ++r) {
+            // wave 0: rotations; wave 1: phases
+            if (lane < half && wv < 2) {
+                int p = rr_player(me, r, lane), q = rr_player(me, r, me - 1 - lane);
+                if (p > q) { const int tmp = p; p = q; q = tmp; }
+                const double2 b = sa[q * ld + p];
+                const double b2 = b.x * b.x + b.y * b.y;
+                if (wv == 0) {
+                    const double d = sa[q * ld + q].x - sa[p * ld + p].x;
+                    JacobiPair j{1.0, 0.0, 0.0, p, q};
+                    if (b2 > kJTiny2) {
+                        const double h = sqrt(fma(d, d, 4.0 * b2)), rr = fabs(d) + h;
+                        const double g = 1.0 / sqrt(2.0 * h * rr), g2 = d >= 0.0 ? 2.0 * g : -2.0 * g;
+                        j.c = rr * g;
+                        j.sr = g2 * b.x;
+                        j.si = -g2 * b.y;
+                    }
+                    pr[lane] = j;
+                } else if (b2 > kJTiny2) {
+                    const double2 u = ph[p];
+                    const double f = sa[q * ld + q].x >= sa[p * ld + p].x ? rsqrt(b2) : -rsqrt(b2);
+                    const double er = f * b.x, ei = -f * b.y;   // e^{-i phi}, with the sign of s
+                    ph[q] = double2{er * u.x - ei * u.y, er * u.y + ei * u.x};
+                }
+            }
+            __syncthreads();
+            // A <- J^H A J in 2 x 2 blocks (rows of pair k1, columns of pair k2), V <- V J
+#pragma unroll
+            for (int u = 0; u < IT; ++u) {
+                const int t = tid + u * nt;
+                if (t < nb2) {
+                    const int k1 = i1[u], k2 = i2[u];
+                    const JacobiPair r1 = pr[k1], c2 = pr[k2];
+                    double2 *pp = sa + c2.p * ld + r1.p, *qp = sa + c2.p * ld + r1.q;   // row p, q of column p
+                    double2 *pq = sa + c2.q * ld + r1.p, *qq = sa + c2.q * ld + r1.q;   // row p, q of column q
+                    double2 a00 = *pp, a10 = *qp, a01 = *pq, a11 = *qq;
+                    jacobi_rotate(c2.c, c2.sr, c2.si, a00, a01);
+                    jacobi_rotate(c2.c, c2.sr, c2.si, a10, a11);
+                    jacobi_rotate(r1.c, r1.sr, -r1.si, a00, a10);
+                    jacobi_rotate(r1.c, r1.sr, -r1.si, a01, a11);
+                    if (k1 == k2) {
+                        a01 = a10 = double2{0.0, 0.0};
+                        a00.y = a11.y = 0.0;
+                    }
+                    *pp = a00;
+                    *qp = a10;
+                    *pq = a01;
+                    *qq = a11;
+                } else if (t < items) {
+                    const int row = i1[u];
+                    const JacobiPair c2 = pr[i2[u]];
+                    jacobi_rotate(c2.c, c2.sr, c2.si, sv[c2.p * ld + row], sv[c2.q * ld + row]);
+                }
+            }
+            __syncthreads();
+        }
+        done = norm2(true) <= limit;
+    }
+    // eigenvalues ascending (ties by index), eigenvectors permuted alike
+    double2 *Vc = reinterpret_cast<double2 *>(V);
+    int *rank_of = reinterpret_cast<int *>(pr);
+    if (tid < m) {
+        const double d = sa[tid * ld + tid].x;
+        int rank = 0;
+        for (int u = 0; u < m; ++u) {
+            const double e = sa[u * ld + u].x;
+            rank += (e < d || (e == d && u < tid)) ? 1 : 0;
+        }
+        w[rank] = ldexp(d, ex);
+        rank_of[tid] = rank;
+        const double2 f = ph[tid];
+        const double n = 1.0 / sqrt(f.x * f.x + f.y * f.y);   // rounding of the product only
+        ph[tid] = double2{f.x * n, f.y * n};
+    }
+    __syncthreads();
+    for (int t = tid; t < m * m; t += nt) {
+        const int r = t % m, c = t / m;
+        const double2 v = sv[c * ld + r], f = ph[c];
+        Vc[(int64_t)rank_of[c] * ldv + r] = double2{v.x * f.x - v.y * f.y, v.x * f.y + v.y * f.x};
+    }
+    if (tid == 0) {
+        status[0] = sweep;
+        status[1] = done ? 1 : 0;
+    }
 }
 
 // partial sums of |A_ij|^2 (off-diagonal only if `off`), one per workgroup, fixed order
@@ -1014,6 +1201,22 @@ int launch_jacobi(int m, double *A, int lda, double *V, int ldv, double *w, int 
     double *part = reinterpret_cast<double *>(base + round_up(2 * (kMaxM / 2) * (2 * sizeof(int) + 3 * sizeof(double)), 256));
     double *sortw = part + round_up(kJNormG * sizeof(double), 256) / sizeof(double);
     const int me = m + (m & 1), half = me / 2;
+    if (m <= kJSmall) {
+        const size_t lds = jacobi_small_lds(me);
+        CHEBFD_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(jacobi_small_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(jacobi_small_lds(kJSmall))));
+        const int items = half * half + half * me;   // 2 x 2 blocks of A and rotated pairs of V per round
+        const int nt = std::max(128, std::min(1024, (items + 63) / 64 * 64));   // at least two waves
+        int *d_status = jr.p, h_status[2];
+        hipLaunchKernelGGL(jacobi_small_kernel, dim3(1), dim3(nt), lds, s, m, me, A, lda, V, ldv, w, max_sweeps, tol,
+                           d_status);
+        CHEBFD_HIP(hipGetLastError());
+        CHEBFD_HIP(hipMemcpyAsync(h_status, d_status, sizeof(h_status), hipMemcpyDeviceToHost, s));
+        CHEBFD_HIP(hipStreamSynchronize(s));
+        *sweeps = h_status[0];
+        *converged = h_status[1];
+        return CHEBFD_OK;
+    }
     const int G = std::min(kJNormG, std::max(1, (m * m + kJW - 1) / kJW));
     double hp[kJNormG];
     auto norm2 = [&](int off, double *out) -> int {
