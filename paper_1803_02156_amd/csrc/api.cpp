@@ -823,6 +823,7 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
         a.G_prev = G;
         a.prog = prog;
         a.epoch = next_step_epoch();
+        a.reverse = (p & 1) ^ 1;
         pend_part = part[flip];
         if (d_eta) {
             pend_eta = d_eta + 2 * ((int64_t)p * n_s + (int64_t)b * n_b);

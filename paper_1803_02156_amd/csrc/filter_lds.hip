@@ -176,15 +176,19 @@ __global__ __launch_bounds__(kThreads) void cheb_lds_kernel(StepArgs a, int tile
     };
 
     int buf = 0;
-    if (begin < end) {
-        fetch(begin);
-        deposit(begin, 0);
+    // forwards, or from the last tile back (a.reverse)
+    const int64_t cnt = begin < end ? (end - begin + stride - 1) / stride : 0;
+    const int64_t step = a.reverse ? -stride : stride;
+    int64_t tile = a.reverse ? begin + (cnt - 1) * stride : begin;
+    if (cnt > 0) {
+        fetch(tile);
+        deposit(tile, 0);
     }
     __syncthreads();
 
-    for (int64_t tile = begin; tile < end; tile += stride) {
-        const bool more = tile + stride < end;
-        if (more) fetch(tile + stride);  // lands in registers while this tile runs
+    for (int64_t k = 0; k < cnt; ++k, tile += step) {
+        const bool more = k + 1 < cnt;
+        if (more) fetch(tile + step);  // lands in registers while this tile runs
 
         const VT *sv = CHEBFD_SV(buf);
         const int32_t *sc = CHEBFD_SC(buf);
@@ -305,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void cheb_lds_kernel(StepArgs a, int tile
           // The next tile's slots go to the idle buffer after the first
           // sub-pass: their loads have landed by then, and the wait for them
           // does not cover the stores of the later sub-passes.
-          if (sp == 0 && more) deposit(tile + stride, buf ^ 1);
+          if (sp == 0 && more) deposit(tile + step, buf ^ 1);
         }
 
         if (more) buf ^= 1;

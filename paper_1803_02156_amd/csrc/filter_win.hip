@@ -8,20 +8,44 @@
 // The sparse product gathers whole row segments of U (NB complex numbers) at
 // the matrix's column indices.  After a locality-preserving row order most of
 // those columns lie close to the row, so one workgroup per CU sweeps a
-// contiguous range of tiles and keeps a window of U in LDS: a ring of
-// kWinBlocks blocks of TR rows (TR = rows of one tile, 16 KB per block).
-// While tile t (rows [t TR, t TR + TR)) is processed the ring holds blocks
-// t - h .. t + h (h = win_halo(TR): 3 tiles of 32 rows, 1 tile of 64) and
-// receives block t + h + 1, which is loaded from HBM once (coalesced, one
-// 16-byte access per thread) and read by the next 2 h + 1 tiles.  Gathers
-// inside the window are LDS reads;
-// columns outside it are gathered from global memory as before.  The vector
-// memory pipeline then carries about one U access per row instead of one per
-// stored entry, plus the streams of W and Y (non-temporal) and the matrix
-// slots (staged in LDS per tile, double buffered).
+// contiguous range of tiles and keeps a window of U in LDS: a ring of blocks of
+// TR rows (TR = rows of one tile, 16 KB per block).  While tile t (rows
+// [t TR, t TR + TR)) is processed the ring holds blocks t - h .. t + h
+// (h = win_halo(TR): 3 tiles of 32 rows, 1 tile of 64) and receives the next
+// block in the direction of the sweep, which is loaded from HBM once and read by
+// the next 2 h + 1 tiles.  Gathers inside the window are LDS reads; columns
+// outside it are gathered from global memory (L2, while the ranges of an XCD
+// advance together).  W and Y are non-temporal streams; the matrix slots are
+// staged in LDS per tile.
 //
-// Lanes: TR = 1024 * CPL / NB rows per tile; lane t works on columns
-// [CPL (t % LPR), CPL (t % LPR) + CPL) of row t / LPR of the tile.
+// What bounds it: memory.  A step has to move U, W in and out, the matrix, and
+// every third step Y in and out; what it fetches beyond that are gathers that
+// miss L2 (FP64 n_b = 32 on the 64x64x32 lattice: about 810 MB against 673 MB).
+// To stay near the rate of a large copy (6 TB/s) a tile must not wait for its own
+// loads:
+//  - The gathers that leave the window are issued one tile ahead, into the
+//    registers that the products read them from (their columns are known: the
+//    slots arrive two tiles ahead, in three LDS buffers), and so are the W rows.
+//    The gathers inside the window go to the registers of the same array, so the
+//    products stay in slot order.
+//  - Y rows (and the W rows of the c64 instance that reads both) are loaded when
+//    the tile starts: held a tile longer they do not fit the 128 registers that
+//    sixteen wavefronts leave each lane.
+//  - The slots are resolved when they are deposited: an LDS offset, or the
+//    complement of a column outside the window.
+//  - The loops over the slots run to the row width, a scalar, also where every
+//    chunk has kWinWidth of them: the branches keep the compiler from moving all
+//    loads of a row to the front, which spills.
+// us per step over a degree-30 filter, before (gathers, W and Y loaded by their
+// own tile) and after; lattice, 4 orbitals:
+//              rows      131072        524288        2097152
+//   FP64 n_b = 32      68 -> 62     233 -> 216     928 -> 901
+//   c64  n_b = 64      71 -> 66     233 -> 216     924 -> 896
+//   c64  n_b = 32         -         128 -> 117     473 -> 452
+//   FP64 n_b = 16         -         141 -> 118     574 -> 476 (LDS-staged kernel before)
+//
+// Lanes: TR = 1024 * 16 / (bytes of a row) rows per tile; lane t works on the
+// 16-byte vector t % LPR of row t / LPR of the tile.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -50,38 +74,42 @@ constexpr int kWinMaxPolls = 200;
 
 template <typename T, int NB>
 struct WinShape {
-    static constexpr int CPL = cols_per_lane<T, NB>();
-    static constexpr int LPR = NB / CPL;               // lanes per row
-    static constexpr int TR = kWinThreads / LPR;       // rows per tile (one per lane group)
+    static constexpr int CV = 8 / sizeof(T);           // complex numbers per 16-byte vector
     static constexpr int RB = NB * 2 * sizeof(T);      // bytes of one row of U
-    static constexpr int RING_ROWS = kWinBlocks * TR;  // power of two
+    static constexpr int LPR = RB / 16;                // lanes per row
+    static constexpr int TR = kWinThreads / LPR;       // rows per tile (one per lane group)
     static constexpr int HALO = win_halo(TR);          // window: tiles t - HALO .. t + HALO
-    static_assert(2 * HALO + 2 <= kWinBlocks, "the window and the incoming block fit the ring");
+    static constexpr int BLOCKS = TR >= 64 ? 4 : 8;    // ring blocks: the window and the incoming block
+    static constexpr int RING_ROWS = BLOCKS * TR;      // power of two
+    static_assert(2 * HALO + 2 <= BLOCKS, "the window and the incoming block fit the ring");
     static constexpr int CPT = TR / 32;                // SELL chunks (C = 32) per tile
 };
 
+// Matrix slots of one tile in LDS: values, and for each slot the byte offset of its row of U in
+// the ring or the complement of its column, if that lies outside the window.
 template <typename T, int MAXW, int TR>
 struct WinMatBuf {
     using VT = typename V2<T>::type;
     static constexpr int SLOTS = TR * MAXW;
     static constexpr int CPT = TR / 32;
     static constexpr int O_VALS = 0;
-    static constexpr int O_COLS = O_VALS + SLOTS * static_cast<int>(sizeof(VT));
-    static constexpr int O_COFF = O_COLS + 4 * SLOTS;
-    static constexpr int O_CW = O_COFF + 4 * (CPT + 1);
+    static constexpr int O_OFFS = O_VALS + SLOTS * static_cast<int>(sizeof(VT));
+    static constexpr int O_COFF = O_OFFS + 4 * SLOTS;
+    static constexpr int O_CW = O_COFF + 4 * CPT;
     static constexpr int BYTES = (O_CW + 4 * CPT + 15) & ~15;
 };
+constexpr int kMatBufs = 3;   // tile t computes, tile t + 1 names its gathers, tile t + 2 arrives
 
 template <typename T, int NB, int MAXW>
 constexpr int win_lds_bytes() {
     using S = WinShape<T, NB>;
-    return S::RING_ROWS * S::RB + 2 * WinMatBuf<T, MAXW, S::TR>::BYTES;
+    return S::RING_ROWS * S::RB + kMatBufs * WinMatBuf<T, MAXW, S::TR>::BYTES;
 }
 
 template <typename T, int NB>
 constexpr bool win_supported() {
     using S = WinShape<T, NB>;
-    return S::TR >= 32 && S::TR % 32 == 0 && S::TR * kWinWidth <= kWinThreads &&
+    return S::TR >= 32 && S::TR % 32 == 0 && S::LPR >= 8 && S::LPR <= 32 &&
            win_lds_bytes<T, NB, kWinWidth>() <= kWinLdsLimit;
 }
 
@@ -112,49 +140,49 @@ __device__ void win_reduce_prev(const StepArgs &a, double *sred) {
 
 }  // namespace
 
-// LDS layout (dynamic): ring[RING_ROWS][RB] | 2 x { vals[SLOTS], cols[SLOTS], coff[CPT + 1], cw[CPT] }.
+// LDS layout (dynamic): ring[RING_ROWS][RB] | kMatBufs x WinMatBuf.
 // The ring area also serves the reductions before the first and after the last tile.
 template <typename T, int NB, int MODE, int MAXW, bool UNI>
 __global__ __launch_bounds__(kWinThreads) void cheb_win_kernel(StepArgs a, int64_t ntiles) {
     using S = WinShape<T, NB>;
     using MB = WinMatBuf<T, MAXW, S::TR>;
     using VT = typename V2<T>::type;
-    using PK = Pack<T, S::CPL>;
-    constexpr int CPL = S::CPL, LPR = S::LPR, TR = S::TR, RB = S::RB;
-    constexpr int CPT = S::CPT;
-    constexpr int HALO = S::HALO;
+    constexpr int CV = S::CV, LPR = S::LPR, TR = S::TR, RB = S::RB, CPT = S::CPT, HALO = S::HALO;
     constexpr int O_MAT = S::RING_ROWS * RB;
+    using PK = Pack<T, CV>;
+    // W rows one tile ahead, unless the registers do not suffice (with them 226 against 216 us
+    // per step, c64 n_b = 64, 524288 rows)
+    constexpr bool kAheadW = !(sizeof(T) == 4 && MODE == kModeStep);
     static_assert(win_supported<T, NB>(), "tile shape does not fit the window kernel");
-    static_assert(MB::SLOTS <= kWinThreads, "one matrix slot per thread and tile");
 
     extern __shared__ __align__(16) unsigned char smem[];
     double *sred = reinterpret_cast<double *>(smem);
 #define CHEBFD_WV(b) reinterpret_cast<VT *>(smem + O_MAT + (b) * MB::BYTES + MB::O_VALS)
-#define CHEBFD_WC(b) reinterpret_cast<int32_t *>(smem + O_MAT + (b) * MB::BYTES + MB::O_COLS)
+#define CHEBFD_WO(b) reinterpret_cast<int32_t *>(smem + O_MAT + (b) * MB::BYTES + MB::O_OFFS)
 #define CHEBFD_WCOFF(b) reinterpret_cast<int32_t *>(smem + O_MAT + (b) * MB::BYTES + MB::O_COFF)
 #define CHEBFD_WCW(b) reinterpret_cast<int32_t *>(smem + O_MAT + (b) * MB::BYTES + MB::O_CW)
-    // byte offset of row q of U inside the ring, plus this lane's columns
-#define CHEBFD_RING(q) reinterpret_cast<const T *>(smem + ((q) & (S::RING_ROWS - 1)) * RB + lane_off)
 
-    const int tid = threadIdx.x;
-    const int jc = (tid % LPR) * CPL;          // first column of this lane
+    const int tid = threadIdx.x, lane = tid & 63;
     const int rr = tid / LPR;                  // row within the tile
-    const int lane_off = jc * 2 * static_cast<int>(sizeof(T));
+    const int lane_off = (tid % LPR) * 16;     // this lane's vector within a row
 
     if (a.part_in != nullptr) win_reduce_prev<NB>(a, sred);
 
-    const T *__restrict__ P = static_cast<const T *>(a.P);
+    const char *const P = static_cast<const char *>(a.P);
+    const char *const O = static_cast<const char *>(a.O);
+    const char *const Y = static_cast<const char *>(a.Y);
     const VT *__restrict__ gval = static_cast<const VT *>(a.val);
     const int32_t *__restrict__ gcol = a.col;
     const T alpha = static_cast<T>(a.alpha), beta = static_cast<T>(a.beta);
     const T g0 = static_cast<T>(a.g0), g1 = static_cast<T>(a.g1), g2 = static_cast<T>(a.g2);
     // row and tile indices fit 32 bits (n < 2^31): scalar loop control stays in SGPRs
     const int n32 = static_cast<int>(a.n);
+    const int nch = static_cast<int>(a.n_chunks);
     const int nblk = (n32 + TR - 1) / TR;
 
-    double e_re[CPL], e_im[CPL], nu[CPL];
+    double e_re[CV], e_im[CV], nu[CV];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) e_re[c] = e_im[c] = nu[c] = 0.0;
+    for (int c = 0; c < CV; ++c) e_re[c] = e_im[c] = nu[c] = 0.0;
 
     // contiguous tile range of this workgroup; each XCD sweeps one eighth
     const int G = gridDim.x, w = blockIdx.x;
@@ -168,221 +196,213 @@ __global__ __launch_bounds__(kWinThreads) void cheb_win_kernel(StepArgs a, int64
         tb = static_cast<int>(ntiles * w / G);
         te = static_cast<int>(ntiles * (w + 1) / G);
     }
+    // sweep direction: tiles ts, ts + dir, ... of [tb, te)
+    const int dir = a.reverse ? -1 : 1, ts = a.reverse ? te - 1 : tb;
+    auto clamp_tile = [&](int tile) { return tile < tb ? tb : tile < te ? tile : te - 1; };
+    // Rows of tile or block `blk` (uniform, inside the matrix) of a block vector: a
+    // uniform base address and this lane's 32-bit offset, its row held to the matrix.
+    auto block_base = [&](const char *x, int blk) { return x + (int64_t)blk * (TR * RB); };
+    auto row_off = [&](int blk) {
+        const int last = n32 - 1 - blk * TR;   // last row of the block that exists
+        return static_cast<uint32_t>((rr < last ? rr : last) * RB + lane_off);
+    };
 
-    // matrix slots of one tile: one slot per thread (prefetch register, then LDS)
-    const int uw = UNI ? MAXW : 0;
-    VT pv = VT{T(0), T(0)};
-    int32_t pc = 0;
-    int pf_ns = 0;
+    // matrix slots of one tile: registers, then LDS.  Threads past the slots repeat the
+    // last one, so that the loads of all tiles are the same instructions and the
+    // compiler can count them.
+    constexpr int MQ = (MB::SLOTS + kWinThreads - 1) / kWinThreads;
+    VT pv[MQ];
+    int32_t pc[MQ];
     int64_t pf_s0 = 0;
-    auto fetch_mat = [&](int64_t tile) {
-        const int64_t c0 = tile * CPT;
-        int64_t c1 = c0 + CPT;
-        if (c1 > a.n_chunks) c1 = a.n_chunks;
-        if (uw > 0) {
-            pf_s0 = c0 * 32 * uw;
-            pf_ns = static_cast<int>((c1 - c0) * 32 * uw);
+    auto fetch_mat = [&](int tile) {
+        const int c0 = tile * CPT, c1 = c0 + CPT < nch ? c0 + CPT : nch;
+        int ns;
+        if constexpr (UNI) {
+            pf_s0 = (int64_t)c0 * 32 * MAXW;
+            ns = (c1 - c0) * 32 * MAXW;
         } else {
             pf_s0 = a.chunk_off[c0];
-            pf_ns = static_cast<int>(a.chunk_off[c1] - pf_s0);
+            ns = static_cast<int>(a.chunk_off[c1] - pf_s0);
         }
-        // non-temporal: each slot is read once, and keeping the slots out of L2
-        // leaves room for the U rows that neighbouring workgroups gather a few
-        // tiles after they were loaded (the gathers that leave the window)
-        if (tid < pf_ns) {
-            pv = ld_nt(gval + pf_s0 + tid);
-            pc = __builtin_nontemporal_load(gcol + pf_s0 + tid);
-        }
-    };
-    auto deposit_mat = [&](int64_t tile, int b) {
-        if (tid < pf_ns) {
-            CHEBFD_WV(b)[tid] = pv;
-            CHEBFD_WC(b)[tid] = pc;
-        }
-        if (uw > 0) return;
-        if (tid < CPT) {
-            const int64_t c = tile * CPT + tid;
-            const bool in = c < a.n_chunks;
-            CHEBFD_WCOFF(b)[tid] = in ? static_cast<int32_t>(a.chunk_off[c] - pf_s0) : 0;
-            CHEBFD_WCW(b)[tid] = in ? a.chunk_width[c] : 0;
+        const VT *const gv = gval + pf_s0;
+        const int32_t *const gc = gcol + pf_s0;
+#pragma unroll
+        for (int q = 0; q < MQ; ++q) {
+            const int s = tid + q * kWinThreads;
+            const uint32_t sl = s < ns ? s : (ns > 0 ? ns - 1 : 0);
+            // non-temporal: each slot is read once, and keeping the slots out of L2
+            // leaves room for the U rows that neighbouring workgroups gather a few
+            // tiles after they were loaded (the gathers that leave the window)
+            pv[q] = ld_nt(gv + sl);
+            pc[q] = __builtin_nontemporal_load(gc + sl);
         }
     };
-    // one block of U rows: row blk * TR + rr, this lane's columns
-    auto ring_store = [&](int blk, const PK &v) {
-        T *dst = reinterpret_cast<T *>(smem + ((blk * TR + rr) & (S::RING_ROWS - 1)) * RB + lane_off);
-        if constexpr (CPL == 2) {
-            *reinterpret_cast<float4 *>(dst) = float4{v.re[0], v.im[0], v.re[1], v.im[1]};
-        } else {
-            *reinterpret_cast<VT *>(dst) = VT{v.re[0], v.im[0]};
+    auto deposit_mat = [&](int tile, int b) {
+        const int wlo = (tile - HALO) * TR;   // window [wlo, wlo + (2 HALO + 1) TR)
+#pragma unroll
+        for (int q = 0; q < MQ; ++q) {
+            const int s = tid + q * kWinThreads;
+            if (s < MB::SLOTS) {
+                const bool in = static_cast<unsigned>(pc[q] - wlo) < static_cast<unsigned>((2 * HALO + 1) * TR);
+                CHEBFD_WV(b)[s] = pv[q];
+                CHEBFD_WO(b)[s] = in ? (pc[q] & (S::RING_ROWS - 1)) * RB : ~pc[q];
+            }
+        }
+        if constexpr (!UNI) {
+            if (tid < CPT) {
+                const int c = tile * CPT + tid;
+                CHEBFD_WCOFF(b)[tid] = c < nch ? static_cast<int32_t>(a.chunk_off[c] - pf_s0) : 0;
+                CHEBFD_WCW(b)[tid] = c < nch ? a.chunk_width[c] : 0;
+            }
         }
     };
-    auto row_ok = [&](int blk) { return blk >= 0 && blk < nblk && blk * TR + rr < n32; };
+    // one block of U rows (blocks outside the matrix: its first or last one, never referenced)
+    auto ring_load = [&](int blk, PK &x) {
+        const int bc = blk < 0 ? 0 : blk < nblk ? blk : nblk - 1;
+        const char *const base = block_base(P, bc);
+        const uint32_t off = row_off(bc);
+        x = load_pack<T, CV, false>(reinterpret_cast<const T *>(base + off));
+    };
+    auto ring_store = [&](int blk, const PK &x) {
+        unsigned char *dst = smem + ((blk * TR + rr) & (S::RING_ROWS - 1)) * RB + lane_off;
+        store_pack<T, CV>(reinterpret_cast<T *>(dst), x);
+    };
 
+    // What a tile finds in registers, loaded while the tile before it ran: its W row, its
+    // resolved slots (LDS byte offset, or ~column outside the window) and the rows of U
+    // outside the window, in the array that the products read.
+    PK o, yv, u[MAXW];
+    int so[MAXW];
+    int base = 0, wdt = UNI ? a.uniform_width : 0;   // first slot and width of the row
+#pragma unroll
+    for (int c = 0; c < CV; ++c) o.re[c] = o.im[c] = yv.re[c] = yv.im[c] = T(0);
+    auto load_row = [&](const char *x, int tile) {
+        return load_pack<T, CV, true>(reinterpret_cast<const T *>(block_base(x, tile) + row_off(tile)));
+    };
+    auto issue_ahead = [&](int tile, int b) {
+        const int cl = rr >> 5;
+        if constexpr (UNI) {
+            base = cl * 32 * MAXW + (rr & 31);
+        } else {
+            // the rows of a wavefront lie in one chunk
+            base = CHEBFD_WCOFF(b)[cl] + (rr & 31);
+            wdt = __builtin_amdgcn_readfirstlane(CHEBFD_WCW(b)[cl]);
+        }
+#pragma unroll
+        for (int k = 0; k < MAXW; ++k) so[k] = k < wdt ? CHEBFD_WO(b)[base + k * 32] : 0;
+#pragma unroll
+        for (int k = 0; k < MAXW; ++k)
+            if (so[k] < 0) {
+                const char *const row = P + ((int64_t)~so[k] * RB + lane_off);
+                u[k] = load_pack<T, CV, false>(reinterpret_cast<const T *>(row));
+            }
+        if constexpr (!mode_first(MODE) && kAheadW) o = load_row(O, tile);
+    };
 
     // (the reduction above ends with a barrier: the ring area is free)
+    int buf = 0;                               // matrix buffer of the current tile
     if (tb < te) {
-        // prologue: the window of the first tile and its matrix slots
+        // prologue: the window of the first tile, the matrix slots of the first two
         PK pro[2 * HALO + 1];
 #pragma unroll
-        for (int q = 0; q < 2 * HALO + 1; ++q) {
-            const int blk = tb - HALO + q;
-            if (row_ok(blk)) pro[q] = load_pack<T, CPL, false>(P + 2 * ((int64_t)(blk * TR + rr) * NB + jc));
-        }
-        fetch_mat(tb);
+        for (int q = 0; q < 2 * HALO + 1; ++q) ring_load(ts - HALO + q, pro[q]);
+        fetch_mat(ts);
 #pragma unroll
-        for (int q = 0; q < 2 * HALO + 1; ++q) {
-            const int blk = tb - HALO + q;
-            if (row_ok(blk)) ring_store(blk, pro[q]);
-        }
-        deposit_mat(tb, 0);
+        for (int q = 0; q < 2 * HALO + 1; ++q) ring_store(ts - HALO + q, pro[q]);
+        deposit_mat(ts, 0);
+        fetch_mat(clamp_tile(ts + dir));
+        deposit_mat(clamp_tile(ts + dir), 1);
+        __syncthreads();
+        issue_ahead(ts, 0);
     }
-    __syncthreads();
 
-    // One tile.  FULL: every row of the tile exists (all tiles but a ragged last
-    // one), so every lane runs the same instruction stream; the partial tile guards
-    // its rows.  (The compiler's wait counts are path-insensitive: a load whose use
-    // sits under a lane-dependent branch stays "pending" at the loop's back edge,
-    // and the next tile then drains the whole memory pipeline before its loads.)
-    int buf = 0;
-    // The previous tile's stored values, kept live (an empty asm statement uses
-    // them) until this tile's loads are issued: otherwise the register allocator
-    // reuses the store's data registers for this tile's gathers, and the compiler
-    // then waits for the store to complete before issuing the next gathers.
-    PK held_w, held_y;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) held_w.re[c] = held_w.im[c] = held_y.re[c] = held_y.im[c] = T(0);
+    // One tile.  FULL: every row of the tile exists (all tiles but a ragged last one).
     auto tile_body = [&](int tile, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
-        const bool more = tile + 1 < te;
-        const int t0 = tile * TR;
-        const int i = t0 + rr;
-        const bool live = FULL || i < n32;
-        const int wlo = t0 - HALO * TR;   // window [wlo, wlo + (2 HALO + 1) TR)
+        const bool live = FULL || tile * TR + rr < n32;
+        const int b1 = buf + 1 < kMatBufs ? buf + 1 : 0, b2 = b1 + 1 < kMatBufs ? b1 + 1 : 0;
         const VT *sv = CHEBFD_WV(buf);
-        const int32_t *sc = CHEBFD_WC(buf);
-
-        // slots of the row (entries past its width gather the row itself with
-        // coefficient 0; when every chunk holds MAXW slots per row the selects fold away)
-        int cc[MAXW];
-        int wdt = MAXW, base = 0;
-        if (live) {
-            const int cl = rr >> 5;
-            base = (UNI ? cl * 32 * MAXW : CHEBFD_WCOFF(buf)[cl]) + (rr & 31);
-            if constexpr (!UNI) wdt = CHEBFD_WCW(buf)[cl];
-#pragma unroll
-            for (int k = 0; k < MAXW; ++k) {
-                const bool act = UNI || k < wdt;
-                cc[k] = act ? sc[base + k * 32] : i;
-            }
-        }
-        // gathers outside the window go to global memory (issued before the
-        // prefetches, so waiting for them leaves the prefetches in flight)
-        PK u[MAXW];
-        bool inw[MAXW];
-        if (live) {
-#pragma unroll
-            for (int k = 0; k < MAXW; ++k) {
-                inw[k] = static_cast<unsigned>(cc[k] - wlo) < static_cast<unsigned>((2 * HALO + 1) * TR);
-                if (!inw[k]) u[k] = load_pack<T, CPL, false>(P + 2 * ((int64_t)cc[k] * NB + jc));
-            }
-        }
-        // prefetches: next tile's matrix slots, W and Y rows; the block entering the window
+        // the block entering the window and the matrix slots of the tile after the next
+        const int blk_in = tile + dir * (HALO + 1);
         PK rf;
-        const int nb_in = tile + HALO + 1;
-        const bool ring_in = more && row_ok(nb_in);
-        if (ring_in) rf = load_pack<T, CPL, false>(P + 2 * ((int64_t)(nb_in * TR + rr) * NB + jc));
-        if (more) fetch_mat(tile + 1);
-#pragma unroll
-        for (int c = 0; c < CPL; ++c)
-            asm volatile("" ::"v"(held_w.re[c]), "v"(held_w.im[c]), "v"(held_y.re[c]), "v"(held_y.im[c]));
-        // row streams of W and Y
-        const int64_t e = 2 * ((int64_t)i * NB + jc);
-        PK o, yv;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) o.re[c] = o.im[c] = yv.re[c] = yv.im[c] = T(0);
-        if (live) {
-            if constexpr (!mode_first(MODE)) o = load_pack<T, CPL, true>(static_cast<const T *>(a.O) + e);
-            if constexpr (MODE == kModeStep) yv = load_pack<T, CPL, true>(static_cast<const T *>(a.Y) + e);
-        }
+        ring_load(blk_in, rf);
+        fetch_mat(clamp_tile(tile + 2 * dir));
 
-        if (live) {
-            PK nw, yo;
-            const PK up = load_pack<T, CPL, false>(CHEBFD_RING(i));
+        if constexpr (MODE == kModeStep) yv = load_row(Y, tile);
+        if constexpr (!mode_first(MODE) && !kAheadW) o = load_row(O, tile);
+        auto lds_vec = [&](int off) {
+            return load_pack<T, CV, false>(reinterpret_cast<const T *>(smem + off + lane_off));
+        };
+        const PK up = lds_vec(((tile * TR + rr) & (S::RING_ROWS - 1)) * RB);
 #pragma unroll
-            for (int k = 0; k < MAXW; ++k)
-                if (inw[k]) u[k] = load_pack<T, CPL, false>(CHEBFD_RING(cc[k]));
-
-            T acc_re[CPL], acc_im[CPL];
+        for (int k = 0; k < MAXW; ++k)
+            if (so[k] >= 0) u[k] = lds_vec(so[k]);
+        T acc_re[CV], acc_im[CV];
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) acc_re[c] = acc_im[c] = T(0);
+        for (int c = 0; c < CV; ++c) acc_re[c] = acc_im[c] = T(0);
 #pragma unroll
-            for (int k = 0; k < MAXW; ++k) {
-                const bool act = UNI || k < wdt;
-                VT h = sv[act ? base + k * 32 : 0];
-                if (!act) h = VT{T(0), T(0)};
+        for (int k = 0; k < MAXW; ++k) {
+            if (k >= wdt) break;
+            const VT h = sv[base + k * 32];
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    acc_re[c] = fma(h.x, u[k].re[c], acc_re[c]);
-                    acc_re[c] = fma(-h.y, u[k].im[c], acc_re[c]);
-                    acc_im[c] = fma(h.x, u[k].im[c], acc_im[c]);
-                    acc_im[c] = fma(h.y, u[k].re[c], acc_im[c]);
-                }
+            for (int c = 0; c < CV; ++c) {
+                acc_re[c] = fma(h.x, u[k].re[c], acc_re[c]);
+                acc_re[c] = fma(-h.y, u[k].im[c], acc_re[c]);
+                acc_im[c] = fma(h.x, u[k].im[c], acc_im[c]);
+                acc_im[c] = fma(h.y, u[k].re[c], acc_im[c]);
             }
+        }
+        PK nw, yo;
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const T hu_re = fma(alpha, acc_re[c], beta * up.re[c]);
-                const T hu_im = fma(alpha, acc_im[c], beta * up.im[c]);
-                if constexpr (mode_first(MODE)) {
-                    nw.re[c] = hu_re;
-                    nw.im[c] = hu_im;
-                } else {
-                    nw.re[c] = fma(T(2), hu_re, -o.re[c]);
-                    nw.im[c] = fma(T(2), hu_im, -o.im[c]);
-                }
+        for (int c = 0; c < CV; ++c) {
+            const T hu_re = fma(alpha, acc_re[c], beta * up.re[c]);
+            const T hu_im = fma(alpha, acc_im[c], beta * up.im[c]);
+            if constexpr (mode_first(MODE)) {
+                nw.re[c] = hu_re;
+                nw.im[c] = hu_im;
+            } else {
+                nw.re[c] = fma(T(2), hu_re, -o.re[c]);
+                nw.im[c] = fma(T(2), hu_im, -o.im[c]);
             }
             if constexpr (MODE == kModeSecond) {
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    yo.re[c] = fma(g0, o.re[c], fma(g1, up.re[c], g2 * nw.re[c]));
-                    yo.im[c] = fma(g0, o.im[c], fma(g1, up.im[c], g2 * nw.im[c]));
-                }
+                yo.re[c] = fma(g0, o.re[c], fma(g1, up.re[c], g2 * nw.re[c]));
+                yo.im[c] = fma(g0, o.im[c], fma(g1, up.im[c], g2 * nw.im[c]));
             } else if constexpr (MODE == kModeStep) {
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    yo.re[c] = add_terms(a.y_terms, g0, o.re[c], g1, up.re[c], g2, nw.re[c], yv.re[c]);
-                    yo.im[c] = add_terms(a.y_terms, g0, o.im[c], g1, up.im[c], g2, nw.im[c], yv.im[c]);
-                }
-            }
-            if constexpr (mode_first(MODE)) {
-                store_pack_nt<T, CPL>(static_cast<T *>(a.N) + e, nw);
-            } else if constexpr (MODE == kModeSecond) {
-                store_pack_nt<T, CPL>(static_cast<T *>(a.N) + e, nw);
-                store_pack_nt<T, CPL>(static_cast<T *>(a.Y) + e, yo);  // Y aliases O: row i's entry is read only here
-            } else {
-                store_pack_nt<T, CPL>(static_cast<T *>(a.O) + e, nw);
-                if constexpr (MODE == kModeStep) store_pack_nt<T, CPL>(static_cast<T *>(a.Y) + e, yo);
-            }
-            held_w = nw;
-            if constexpr (MODE == kModeSecond || MODE == kModeStep) held_y = yo;
-            if constexpr (mode_dots(MODE)) {
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) {
-                    const double nr = nw.re[c], ni = nw.im[c], ur = up.re[c], ui = up.im[c];
-                    e_re[c] = fma(nr, ur, fma(ni, ui, e_re[c]));
-                    e_im[c] = fma(nr, ui, fma(-ni, ur, e_im[c]));
-                    nu[c] = fma(ur, ur, fma(ui, ui, nu[c]));
-                }
+                yo.re[c] = add_terms(a.y_terms, g0, o.re[c], g1, up.re[c], g2, nw.re[c], yv.re[c]);
+                yo.im[c] = add_terms(a.y_terms, g0, o.im[c], g1, up.im[c], g2, nw.im[c], yv.im[c]);
             }
         }
-        // block tile + HALO + 1 replaces block tile - HALO - 1 (outside
-        // this tile's window); the next tile's slots go to the idle buffer.  Their
-        // loads were issued before the W and Y loads and the stores, so the wait
-        // for them leaves those in flight; the stores also stay in flight across
-        // the barrier (it orders LDS only; no other row reads this row's W or Y).
-        if (ring_in) ring_store(nb_in, rf);
-        if (more) deposit_mat(tile + 1, buf ^ 1);
+        if (mode_dots(MODE) && live) {
+#pragma unroll
+            for (int c = 0; c < CV; ++c) {
+                const double nr = nw.re[c], ni = nw.im[c], ur = up.re[c], ui = up.im[c];
+                e_re[c] = fma(nr, ur, fma(ni, ui, e_re[c]));
+                e_im[c] = fma(nr, ui, fma(-ni, ur, e_im[c]));
+                nu[c] = fma(ur, ur, fma(ui, ui, nu[c]));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the next tile's loads (its matrix slots were deposited one tile ago); the last
+        // tile of the range repeats its own
+        const int next = clamp_tile(tile + dir);
+        issue_ahead(next, next != tile ? b1 : buf);
+        __builtin_amdgcn_sched_barrier(0);
+        if (live) {
+            auto out = [&](void *x) {
+                return reinterpret_cast<T *>(static_cast<char *>(x) + (int64_t)tile * (TR * RB) + (rr * RB + lane_off));
+            };
+            store_pack_nt<T, CV>(out(mode_first(MODE) || MODE == kModeSecond ? a.N : a.O), nw);
+            // Second: Y aliases O, whose row is read only here (one tile ago)
+            if constexpr (MODE == kModeSecond || MODE == kModeStep) store_pack_nt<T, CV>(out(a.Y), yo);
+        }
+        // the block entering the window replaces one that has left it (the ring holds at least
+        // 2 HALO + 2 blocks); the matrix slots go to the buffer that the tile before this one
+        // used.  The stores stay in flight across the barrier (it orders LDS only; no other
+        // row reads this row's W or Y).
+        ring_store(blk_in, rf);
+        deposit_mat(clamp_tile(tile + 2 * dir), b2);
         __syncthreads();
-        buf ^= 1;
+        buf = b1;
     };
     // Lead control between the sweep ranges of one XCD.  The row order deals
     // neighbouring pencils of the lattice to the ranges of one XCD at equal
@@ -415,54 +435,59 @@ __global__ __launch_bounds__(kWinThreads) void cheb_win_kernel(StepArgs a, int64
         }
     };
 
-    // full tiles, then the ragged last tile of the matrix (if it is in this range)
+    // full tiles, and the ragged last tile of the matrix (if it is in this range) after or before them
     const int te_full = te < n32 / TR ? te : (n32 / TR > tb ? n32 / TR : tb);
-    for (int tile = tb; tile < te_full; ++tile) {
-        if (lead && wave == 0 && (tile - tb) % kWinCheckEvery == 0) check(tile - tb);
+    if (dir < 0)
+        for (int tile = te - 1; tile >= te_full; --tile) tile_body(tile, std::false_type{});
+    const int full = te_full - tb;
+    int tile = dir > 0 ? tb : te_full - 1;
+    for (int k = 0; k < full; ++k, tile += dir) {
+        if (lead && wave == 0 && k % kWinCheckEvery == 0) check(k);
         tile_body(tile, std::true_type{});
     }
-    for (int tile = te_full; tile < te; ++tile) tile_body(tile, std::false_type{});
+    if (dir > 0)
+        for (; tile < te; ++tile) tile_body(tile, std::false_type{});
     if (lead && wave == 0)
         __hip_atomic_store(my_prog, tag | static_cast<uint32_t>(te - tb), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     if constexpr (!mode_dots(MODE)) return;
     if (a.part_out == nullptr) return;
-    // workgroup reduction over the TR lanes of each column, fixed order;
-    // sred[(component * CPL + c) * kWinThreads + lane] (over the ring: every
-    // wave has passed the last barrier of the tile loop)
+    // sums of a column: over the rows of a wavefront by lane exchanges, then over the
+    // wavefronts through LDS (over the ring: every wave has passed the last barrier)
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        sred[(0 * CPL + c) * kWinThreads + tid] = e_re[c];
-        sred[(1 * CPL + c) * kWinThreads + tid] = e_im[c];
-        sred[(2 * CPL + c) * kWinThreads + tid] = nu[c];
+    for (int c = 0; c < CV; ++c) {
+#pragma unroll
+        for (int m = LPR; m < 64; m <<= 1) {
+            e_re[c] += __shfl_xor(e_re[c], m);
+            e_im[c] += __shfl_xor(e_im[c], m);
+            nu[c] += __shfl_xor(nu[c], m);
+        }
+        if (lane < LPR) {
+            double *const sw = sred + (tid >> 6) * (3 * NB) + lane * CV + c;
+            sw[0] = e_re[c];
+            sw[NB] = e_im[c];
+            sw[2 * NB] = nu[c];
+        }
     }
     __syncthreads();
-    if (tid < NB) {
-        const int lj = tid / CPL, c = tid % CPL;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for (int q = 0; q < TR; ++q) {
-            s0 += sred[(0 * CPL + c) * kWinThreads + q * LPR + lj];
-            s1 += sred[(1 * CPL + c) * kWinThreads + q * LPR + lj];
-            s2 += sred[(2 * CPL + c) * kWinThreads + q * LPR + lj];
-        }
-        a.part_out[(int64_t)(0 * NB + tid) * G + w] = s0;
-        a.part_out[(int64_t)(1 * NB + tid) * G + w] = s1;
-        a.part_out[(int64_t)(2 * NB + tid) * G + w] = s2;
+    for (int q = tid; q < 3 * NB; q += kWinThreads) {
+        double s = 0.0;
+#pragma unroll
+        for (int x = 0; x < kWinThreads / 64; ++x) s += sred[x * (3 * NB) + q];
+        a.part_out[(int64_t)q * G + w] = s;
     }
 }
 #undef CHEBFD_WV
-#undef CHEBFD_WC
+#undef CHEBFD_WO
 #undef CHEBFD_WCOFF
 #undef CHEBFD_WCW
-#undef CHEBFD_RING
 
 namespace {
 
 template <typename T, int NB, int MODE, int MAXW, bool UNI>
 int launch_win_one(const StepArgs &a, const WinGeometry &g, hipStream_t s) {
     constexpr int lds = win_lds_bytes<T, NB, MAXW>();
-    hipLaunchKernelGGL((cheb_win_kernel<T, NB, MODE, MAXW, UNI>), dim3(g.G), dim3(kWinThreads), lds, s, a,
-                       g.ntiles);
+    hipLaunchKernelGGL((cheb_win_kernel<T, NB, MODE, MAXW, UNI>), dim3(g.G), dim3(kWinThreads), lds, s, a, g.ntiles);
     CHEBFD_HIP(hipGetLastError());
     return CHEBFD_OK;
 }
@@ -511,20 +536,23 @@ bool win_geometry(const chebfd_matrix *H, int prec, int nb, int num_cus, WinGeom
     if (H->C != 32 || H->max_width > kWinWidth) return false;
     int tr;
     // instances where the window beats the LDS-staged kernel (measured): FP64
-    // n_b = 32, c64 n_b = 64, and c64 n_b = 32 from 32 tiles of 64 rows per CU
-    // (the 64x64x32 lattice: 141 against 151 us per step)
+    // n_b = 32, c64 n_b = 64, and rows of 256 bytes (c64 n_b = 32 and FP64 n_b = 16)
+    // from 32 tiles of 64 rows per CU (the 64x64x32 lattice: 117 and 118 against
+    // 151 and 141 us per step; 131072 rows: 31 us either way)
     if (prec == CHEBFD_PREC_FP64 && nb == 32)
         tr = WinShape<double, 32>::TR;
     else if (prec == CHEBFD_PREC_MIXED && nb == 64)
         tr = WinShape<float, 64>::TR;
-    else if (prec == CHEBFD_PREC_MIXED && nb == 32 && H->n >= (int64_t)kWinC64Nb32Tiles * num_cus * 64)
+    else if (prec == CHEBFD_PREC_MIXED && nb == 32 && H->n >= (int64_t)kWinNarrowTiles * num_cus * 64)
         tr = WinShape<float, 32>::TR;
+    else if (prec == CHEBFD_PREC_FP64 && nb == 16 && H->n >= (int64_t)kWinNarrowTiles * num_cus * 64)
+        tr = WinShape<double, 16>::TR;
     else
         return false;
     const int local = H->window_local[tr == 32 ? 0 : 1];
     if (local < kWinMinLocal) return false;
     g->tr = tr;
-    // every chunk exactly kWinWidth slots wide (lattice Hamiltonians of 4 orbitals): no width selects
+    // every chunk exactly kWinWidth slots wide (lattice Hamiltonians of 4 orbitals): no chunk tables
     g->uniform = H->uniform_width == kWinWidth ? 1 : 0;
     g->ntiles = (H->n + tr - 1) / tr;
     // one workgroup per CU, at least two tiles each (the window needs a sweep to pay off)
@@ -534,7 +562,8 @@ bool win_geometry(const chebfd_matrix *H, int prec, int nb, int num_cus, WinGeom
     static bool attr_ok =
         set_win_attr<double, 32, kWinWidth, true>() && set_win_attr<double, 32, kWinWidth, false>() &&
         set_win_attr<float, 64, kWinWidth, true>() && set_win_attr<float, 64, kWinWidth, false>() &&
-        set_win_attr<float, 32, kWinWidth, true>() && set_win_attr<float, 32, kWinWidth, false>();
+        set_win_attr<float, 32, kWinWidth, true>() && set_win_attr<float, 32, kWinWidth, false>() &&
+        set_win_attr<double, 16, kWinWidth, true>() && set_win_attr<double, 16, kWinWidth, false>();
     if (!attr_ok) return false;
     g->G = static_cast<int>(G);
     return true;
@@ -544,6 +573,7 @@ int launch_win_step(int prec, int nb, int mode, const StepArgs &a, const WinGeom
     if (prec == CHEBFD_PREC_FP64 && nb == 32) return launch_win_w<double, 32>(mode, a, g, s);
     if (prec == CHEBFD_PREC_MIXED && nb == 64) return launch_win_w<float, 64>(mode, a, g, s);
     if (prec == CHEBFD_PREC_MIXED && nb == 32) return launch_win_w<float, 32>(mode, a, g, s);
+    if (prec == CHEBFD_PREC_FP64 && nb == 16) return launch_win_w<double, 16>(mode, a, g, s);
     CHEBFD_FAIL(CHEBFD_EINVAL, "window kernel has no instance for prec %d, n_b = %d", prec, nb);
 }
 

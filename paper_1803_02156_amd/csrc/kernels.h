@@ -60,6 +60,11 @@ struct StepArgs {
     int32_t uniform_width;      // every chunk has this many slots per row (0: read chunk_width)
     int64_t *prog;              // [G] progress words of the window kernel's lead control, or null
     int32_t epoch;              // this launch's tag in prog (nonzero, distinct from recent launches)
+    int32_t reverse;            // sweep the rows from the last to the first (window and LDS-staged kernels):
+                                // every other launch of a filter, so that a launch starts on the rows
+                                // the one before it ended on, which the 256 MB memory-side cache still
+                                // holds (us per launch with Y update, FP64 n_b = 32: 278 -> 271 at
+                                // 524288 rows, 1196 -> 1169 at 2097152)
 };
 // A fresh launch tag for StepArgs::epoch (host, thread-safe).
 int32_t next_step_epoch();
@@ -106,22 +111,21 @@ struct WaveGeometry {
 bool wave_geometry(const chebfd_matrix *H, int prec, int nb, WaveGeometry *g);
 int launch_wave_step(int prec, int nb, int mode, const StepArgs &a, const WaveGeometry &g, hipStream_t s);
 int launch_wave_reduce(int nb, const StepArgs &a, hipStream_t s);
-// Window step kernel (filter_win.hip): one 1024-thread workgroup per CU sweeps
-// a contiguous range of tiles and gathers from a ring of U rows staged in LDS
-// (kWinBlocks blocks of one tile each; tile t reads blocks t - h .. t + h,
-// h = win_halo(tile rows)).  Used for FP64 n_b = 32, c64 n_b = 64 and c64
-// n_b = 32, rows of at most kWinWidth entries, when at least kWinMinLocal of
-// 1000 stored entries fall inside the window.
-constexpr int kWinBlocks = 8;
+// Window step kernel (filter_win.hip): one workgroup per CU sweeps a
+// contiguous range of tiles and gathers from a ring of U rows staged in LDS
+// (blocks of one tile each; tile t reads blocks t - h .. t + h,
+// h = win_halo(tile rows)).  Used for FP64 n_b = 32 and 16, c64 n_b = 64 and
+// 32, rows of at most kWinWidth entries, when at least kWinMinLocal of 1000
+// stored entries fall inside the window.
 // Window half-width in tiles: 3 tiles of 32 rows, 1 tile of 64 rows.  The
 // z-neighbours of 4 x 4 pencils (4 orbitals) lie 64 rows away; with 32-row
-// tiles a window of 2 tiles measured 7 % slower than 3, with 64-row tiles 1
-// tile beats 3 (fewer prologue blocks: 64x64x32 c64 n_b = 32 step 151.6 ->
+// tiles a window of 2 tiles measured 5 % slower than 3 from 262144 to 1048576
+// rows (and 4 % faster at 2097152), with 64-row tiles 1 tile beats 3 (fewer prologue blocks: 64x64x32 c64 n_b = 32 step 151.6 ->
 // 141.1 us).
 constexpr int win_halo(int tr) { return tr >= 64 ? 1 : 3; }
 constexpr int kWinWidth = 13;       // rows of at most this many stored entries
 constexpr int kWinMinLocal = 700;
-constexpr int kWinC64Nb32Tiles = 32;   // c64 n_b = 32 takes the window kernel from this many 64-row tiles per CU
+constexpr int kWinNarrowTiles = 32;   // rows of 256 bytes (FP64 n_b = 16, c64 n_b = 32): from this many 64-row tiles per CU
 struct WinGeometry {
     int tr;             // rows per tile
     int uniform;        // 1: every chunk holds exactly kWinWidth slots per row
