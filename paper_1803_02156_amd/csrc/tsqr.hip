@@ -16,14 +16,18 @@
 //     registers; per Householder step the owner of the pivot column puts its
 //     reflector in LDS and the other columns form their products with it by a
 //     32-lane sum (DPP within rows of 16 lanes, one permute across; one barrier
-//     per step); the node's explicit Q is then formed in place from its
-//     reflectors.  The leaves are the 256-row
+//     per step); the node keeps its reflectors V.  The leaves are the 256-row
 //     ranges of T; a node of the next level stacks the R factors of 256 / PW
 //     children.  The root's R is the panel's diagonal block of R after a phase
 //     per column makes its diagonal real positive (the phase goes into Q);
 //   * the explicit Q of the panel is the product down the tree: each node's Q
-//     times the PW x PW block of its parent's product that belongs to it,
-//     staged through LDS so that the product can overwrite the node's Q.
+//     times the PW x PW block M of its parent's product that belongs to it, without
+//     forming the node's Q: H_0 ... H_{PW-1} = I - V T V^H with
+//     T^-1 = diag(1 / c) + the strict upper part of V^H V (c_k = 2 / |v_k|^2), so
+//     the node's rows are [M; 0] - V W with T^-1 W = (top block of V)^H M: one MFMA
+//     product V^H V, one triangular solve and the product with W that a node's
+//     explicit Q would have taken too.  V is staged in LDS, so the rows can
+//     overwrite it.
 // Reflector of a column x (rows k..): u = x - beta e_k with
 // beta = -(x_k / |x_k|) ||x||, H = I - u u^H / (||x|| (||x|| + |x_k|)), H x = beta e_k.
 #include <hip/hip_runtime.h>
@@ -44,9 +48,9 @@ constexpr int kRpl = kNode / 32;  // rows per lane
 constexpr int kEw = 256;        // threads of the elementwise kernels
 
 constexpr int node_threads(int pw) { return ((pw + 1) / 2) * 64; }
-constexpr int apply_cg(int pw) { return pw < 8 ? pw : 8; }  // output columns per thread
-constexpr int apply_threads(int pw) { return kNode * (pw / apply_cg(pw)); }
-constexpr size_t apply_lds_bytes(int pw) { return (size_t)(kNode * (pw + 1) + pw * pw) * 16; }
+constexpr int apply_threads(int pw) { return pw <= 8 ? kNode : kNode * (pw / 8); }
+// V rows, the block M (then W) and the upper triangle of V^H V
+constexpr size_t apply_lds_bytes(int pw) { return (size_t)(kNode * (pw + 1) + pw * pw + pw * (pw + 1) / 2) * 16; }
 
 __device__ inline double2 ld_c(const void *base, int prec, int64_t idx) {
     if (prec == CHEBFD_PREC_FP64) return static_cast<const double2 *>(base)[idx];
@@ -84,6 +88,16 @@ __device__ inline double sum32(double v) {
     return v;
 }
 
+// value of lane k (uniform) of this lane's half-wave
+__device__ inline double half_bcast(double v, int k) {
+    const long long b = __double_as_longlong(v);
+    const int lo = static_cast<int>(b), hi = static_cast<int>(b >> 32);
+    const bool upper = (threadIdx.x & 32) != 0;
+    const int l = upper ? __builtin_amdgcn_readlane(lo, k + 32) : __builtin_amdgcn_readlane(lo, k);
+    const int h = upper ? __builtin_amdgcn_readlane(hi, k + 32) : __builtin_amdgcn_readlane(hi, k);
+    return __longlong_as_double((static_cast<long long>(h) << 32) | static_cast<unsigned int>(l));
+}
+
 __device__ inline double2 cmul(double2 a, double2 b) { return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ inline double2 cjmul(double2 a, double2 b) {  // conj(a) b
     return double2{a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x};
@@ -94,7 +108,7 @@ __device__ inline double2 unit_phase(double2 z) {
 }
 
 // Householder QR of the 256-row node blockIdx.x of `in` (rows >= `rows` read
-// as zero; columns >= cols not touched).  Writes the node's explicit Q (rows <
+// as zero; columns >= cols not touched).  Writes the node's reflectors (rows <
 // rows) to q (FP64, row i at q + i PW; q may equal in) and its R either to
 // rnext (rows [PW node, PW node + PW), PW wide, zeros below the diagonal) or,
 // at the root, phase-normalised to rroot (cols x cols, column-major, ldr).
@@ -189,113 +203,183 @@ __global__ __launch_bounds__(node_threads(PW)) void tsqr_node_kernel(const void 
             rnext[((int64_t)blockIdx.x * PW + i) * PW + j] = v;
         }
     }
-    __syncthreads();   // the last reflector's buffer is reused below
-
-    // --- explicit Q = H_0 ... H_{cols-1} [I; 0], formed in place from the last reflector back ---
-    for (int k = cols - 1; k >= 0; --k) {
-        const int b = k & 1;
-        if (j == k) {
-#pragma unroll
-            for (int s = 0; s < kRpl; ++s) {
-                const int i = l32 + 32 * s;
-                ub[b][i] = i >= k ? a[s] : double2{0.0, 0.0};
-            }
-        }
-        __syncthreads();
-        const double c = cs[k];
-        if (own && j > k) {
-            double2 u[kRpl];
-            double wr = 0.0, wi = 0.0;
-#pragma unroll
-            for (int s = 0; s < kRpl; ++s) {
-                u[s] = ub[b][l32 + 32 * s];
-                const double2 t = cjmul(u[s], a[s]);
-                wr += t.x;
-                wi += t.y;
-            }
-            const double2 cw{c * sum32(wr), c * sum32(wi)};
-#pragma unroll
-            for (int s = 0; s < kRpl; ++s) {
-                const double2 t = cmul(u[s], cw);
-                a[s].x -= t.x;
-                a[s].y -= t.y;
-            }
-        } else if (j == k) {
-            // H_k e_k = e_k - c u conj(u_k)
-            const double2 ukk = ub[b][k];
-            const double2 f{c * ukk.x, -c * ukk.y};
-#pragma unroll
-            for (int s = 0; s < kRpl; ++s) {
-                const int i = l32 + 32 * s;
-                double2 v{0.0, 0.0};
-                if (i >= k) {
-                    const double2 t = cmul(a[s], f);
-                    v = double2{(i == k ? 1.0 : 0.0) - t.x, -t.y};
-                }
-                a[s] = v;
-            }
-        }
-    }
-    if (root && own) {
-        const double2 d = unit_phase(rd[j]);
-#pragma unroll
-        for (int s = 0; s < kRpl; ++s) a[s] = cmul(a[s], d);
-    }
 #pragma unroll
     for (int s = 0; s < kRpl; ++s) {
-        const int64_t g = r0 + l32 + 32 * s;
-        if (own && g < rows) q[g * PW + j] = a[s];
+        const int i = l32 + 32 * s;
+        const int64_t g = r0 + i;
+        if (own && g < rows) q[g * PW + j] = i >= j ? a[s] : double2{0.0, 0.0};
     }
 }
 
-// out(rows of node blockIdx.x) = q(rows of the node) M_node, M_node = rows
-// [PW node, PW node + PW) of m (PW wide), or the identity when m is null.
-// The node's rows of q and M_node are staged in LDS first, so out may be q.
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// out(rows of node blockIdx.x) = H_0 ... H_{cols-1} [M; 0] for the reflectors in q's rows of
+// the node and M = rows [PW node, PW node + PW) of m (PW wide); at the root (m null) M is the
+// diagonal of phases that make R's diagonal real positive.  Everything is staged in LDS
+// first, so out may be q.
+//
+// What bounds it: one workgroup per CU (LDS) works through five dependent stages (load, V^H V,
+// the solve, V W, store): 332 us for 2048 nodes at PW = 32 (8 per CU), 32 us for one.  The
+// products run on the matrix cores; with V W on the VALU and a division per step of the solve
+// the 2048 nodes took 425 us.  It takes the place of forming each node's Q from its reflectors
+// one at a time (a barrier and a 32-lane sum each): TSQR of 524288 x 128 FP64 7.8 -> 7.0 ms.
 template <int PW>
 __global__ __launch_bounds__(apply_threads(PW)) void tsqr_apply_kernel(const double2 *q, int64_t rows, int cols,
                                                                        const double2 *m, void *out, int prec,
                                                                        int64_t ld) {
     extern __shared__ double2 lds[];
-    constexpr int CG = apply_cg(PW), NG = PW / CG, NT = apply_threads(PW), SQ = PW + 1;
-    double2 *sq = lds;                 // [kNode][PW + 1]
-    double2 *sm = lds + kNode * SQ;    // [PW][PW]
+    constexpr int NT = apply_threads(PW), SQ = PW + 1;
+    double2 *sq = lds;                 // [kNode][PW + 1]: V
+    double2 *sm = lds + kNode * SQ;    // [PW][PW]: M, then W
+    double2 *sg = sm + PW * PW;        // G = V^H V, entry (i, k), i <= k, at k (k + 1) / 2 + i
+    const int tid = threadIdx.x, lane = tid & 63;
     const int64_t r0 = (int64_t)blockIdx.x * kNode;
-    for (int t = threadIdx.x; t < kNode * PW; t += NT) {
+    for (int t = tid; t < kNode * PW; t += NT) {
         const int rr = t / PW, cc = t % PW;
         const int64_t g = r0 + rr;
         sq[rr * SQ + cc] = (g < rows && cc < cols) ? q[g * PW + cc] : double2{0.0, 0.0};
     }
-    for (int t = threadIdx.x; t < PW * PW; t += NT) {
-        const int kk = t / PW, cc = t % PW;
-        double2 v{0.0, 0.0};
-        if (kk < cols && cc < cols) {
-            if (m)
-                v = m[((int64_t)blockIdx.x * PW + kk) * PW + cc];
-            else
-                v = double2{kk == cc ? 1.0 : 0.0, 0.0};
+    if (m)
+        for (int t = tid; t < PW * PW; t += NT) {
+            const int kk = t / PW, cc = t % PW;
+            sm[t] = kk < cols && cc < cols ? m[((int64_t)blockIdx.x * PW + kk) * PW + cc] : double2{0.0, 0.0};
         }
-        sm[kk * PW + cc] = v;
-    }
     __syncthreads();
-    const int r = threadIdx.x / NG, c0 = (threadIdx.x % NG) * CG;
-    double2 acc[CG];
-#pragma unroll
-    for (int c = 0; c < CG; ++c) acc[c] = double2{0.0, 0.0};
-    for (int k = 0; k < cols; ++k) {
-        const double2 x = sq[r * SQ + k];
-#pragma unroll
-        for (int c = 0; c < CG; ++c) {
-            const double2 y = sm[k * PW + c0 + c];
-            acc[c].x += x.x * y.x - x.y * y.y;
-            acc[c].y += x.x * y.y + x.y * y.x;
+
+    // --- V^H V: a wave forms the real or the imaginary part of one 16 x 16 tile over one of KS
+    // row ranges; the ranges are added in turn ---
+    constexpr int NTILE = PW > 16 ? 3 : 1, UNITS = 2 * NTILE, KS = NT / 64 / UNITS < 4 ? NT / 64 / UNITS : 4;
+    static_assert(KS >= 1 && kNode % (4 * KS) == 0, "row ranges of the V^H V product");
+    const int unit = (tid >> 6) % UNITS, part = (tid >> 6) / UNITS;
+    const int ti = unit / 2 == 2 ? 16 : 0, tj = unit / 2 == 0 ? 0 : 16;   // tiles (0,0), (0,1), (1,1)
+    const bool imag = unit & 1;
+    v4d d{0.0, 0.0, 0.0, 0.0};
+    if (part < KS) {
+        const int ci = ti + (lane & 15), cj = tj + (lane & 15);
+        const int b = part * (kNode / KS) + (lane >> 4);
+#pragma unroll 4
+        for (int r = 0; r < kNode / KS; r += 4) {
+            const double2 x = ci < PW ? sq[(b + r) * SQ + ci] : double2{0.0, 0.0};
+            const double2 y = cj < PW ? sq[(b + r) * SQ + cj] : double2{0.0, 0.0};
+            d = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, imag ? y.y : y.x, d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f64_16x16x4f64(imag ? -x.y : x.y, imag ? y.x : y.y, d, 0, 0, 0);
         }
     }
-    const int64_t g = r0 + r;
-    if (g < rows) {
+    for (int p = 0; p < KS; ++p) {
+        if (part == p) {
 #pragma unroll
-        for (int c = 0; c < CG; ++c)
-            if (c0 + c < cols) st_c(out, prec, g * ld + c0 + c, acc[c]);
+            for (int e = 0; e < 4; ++e) {
+                const int i = ti + (lane >> 4) + 4 * e, k = tj + (lane & 15);
+                if (i <= k && k < PW) {
+                    double *const g = reinterpret_cast<double *>(sg + k * (k + 1) / 2 + i) + (imag ? 1 : 0);
+                    *g = p == 0 ? d[e] : *g + d[e];
+                }
+            }
+        }
+        __syncthreads();
     }
+    if (!m) {
+        for (int t = tid; t < PW * PW; t += NT) {
+            const int kk = t / PW, cc = t % PW;
+            double2 v{0.0, 0.0};
+            if (kk == cc && kk < cols) {
+                // the reflector maps its column to -ph |x| e_k, its own entry k is ph (|x_k| + |x|)
+                const double2 ph = unit_phase(sq[kk * SQ + kk]);
+                v = sg[kk * (kk + 1) / 2 + kk].x > 0.0 ? double2{-ph.x, -ph.y} : double2{1.0, 0.0};
+            }
+            sm[t] = v;
+        }
+        __syncthreads();
+    }
+
+    // G_ik c_k above the diagonal, c_k in the imaginary part of the diagonal
+    for (int t = tid; t < PW * PW; t += NT) {
+        const int i = t / PW, k = t % PW;
+        if (i > k) continue;
+        const double gk = sg[k * (k + 1) / 2 + k].x;
+        const double c = gk > 0.0 ? 2.0 / gk : 0.0;
+        double2 *const e = sg + k * (k + 1) / 2 + i;
+        if (i == k)
+            e->y = c;
+        else
+            *e = double2{c * e->x, c * e->y};
+    }
+
+    // --- Z = (top block of V)^H M, then W = T Z by back substitution: a half-wave per column,
+    // its lane l32 holding row l32 ---
+    const int l32 = lane & 31, hc = tid >> 5;
+    const int li = l32 < PW ? l32 : 0;
+    double2 z{0.0, 0.0};
+    if (hc < PW)
+#pragma unroll 4
+        for (int i = 0; i < PW; ++i) {
+            const double2 t = cjmul(sq[i * SQ + li], sm[i * PW + hc]);
+            z.x += t.x;
+            z.y += t.y;
+        }
+    __syncthreads();
+    if (hc < PW) {
+#pragma unroll 4
+        for (int k = PW - 1; k > 0; --k) {
+            const double2 zk{half_bcast(z.x, k), half_bcast(z.y, k)};
+            if (l32 < k) {
+                const double2 t = cmul(sg[k * (k + 1) / 2 + li], zk);
+                z.x -= t.x;
+                z.y -= t.y;
+            }
+        }
+        const double c = sg[li * (li + 1) / 2 + li].y;
+        z.x *= c;
+        z.y *= c;
+    }
+
+    // --- [M; 0] - V W: a wave forms RT row tiles of 16 by CT column tiles ---
+    constexpr int RT = kNode / 16 / (NT / 64), CT = PW > 16 ? 2 : 1;
+    const int l16 = lane & 15, q4 = lane >> 4, rw = (tid >> 6) * (RT * 16);
+    v4d dr[RT][CT], di[RT][CT];
+#pragma unroll
+    for (int a = 0; a < RT; ++a)
+#pragma unroll
+        for (int b = 0; b < CT; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = rw + 16 * a + q4 + 4 * e, c = 16 * b + l16;
+                const bool in = r < PW && c < PW;
+                dr[a][b][e] = in ? sm[r * PW + c].x : 0.0;
+                di[a][b][e] = in ? sm[r * PW + c].y : 0.0;
+            }
+    __syncthreads();
+    if (hc < PW && l32 < PW) sm[l32 * PW + hc] = z;
+    __syncthreads();
+#pragma unroll 2
+    for (int k0 = 0; k0 < PW; k0 += 4) {
+        const int k = k0 + q4;
+        double2 w[CT];
+#pragma unroll
+        for (int b = 0; b < CT; ++b)
+            w[b] = k < PW && 16 * b + l16 < PW ? sm[k * PW + 16 * b + l16] : double2{0.0, 0.0};
+#pragma unroll
+        for (int a = 0; a < RT; ++a) {
+            const double2 v = k < PW ? sq[(rw + 16 * a + l16) * SQ + k] : double2{0.0, 0.0};
+#pragma unroll
+            for (int b = 0; b < CT; ++b) {
+                dr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.x, w[b].x, dr[a][b], 0, 0, 0);
+                dr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, w[b].y, dr[a][b], 0, 0, 0);
+                di[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.x, w[b].y, di[a][b], 0, 0, 0);
+                di[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, w[b].x, di[a][b], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < RT; ++a)
+#pragma unroll
+        for (int b = 0; b < CT; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t g = r0 + rw + 16 * a + q4 + 4 * e;
+                const int c = 16 * b + l16;
+                if (g < rows && c < cols) st_c(out, prec, g * ld + c, double2{dr[a][b][e], di[a][b][e]});
+            }
 }
 
 // Off-diagonal blocks of the panel's columns c0 .. c0 + cols - 1 of R:
@@ -378,11 +462,11 @@ int tsqr_panel_t(int64_t n, int cols, const void *src, int prec_src, int64_t ld_
                            arr[l], l < L ? arr[l + 1] : nullptr, l == L ? 1 : 0, R, ldr);
         CHEBFD_HIP(hipGetLastError());
     }
-    for (int l = L > 0 ? L - 1 : 0; l >= 0; --l) {
+    for (int l = L; l >= 0; --l) {
         const unsigned nodes = static_cast<unsigned>((rows[l] + kNode - 1) / kNode);
         void *out = l == 0 ? dst : static_cast<void *>(arr[l]);
         hipLaunchKernelGGL(tsqr_apply_kernel<PW>, dim3(nodes), dim3(apply_threads(PW)), apply_lds_bytes(PW), s,
-                           arr[l], rows[l], cols, L > 0 ? arr[l + 1] : nullptr, out,
+                           arr[l], rows[l], cols, l < L ? arr[l + 1] : nullptr, out,
                            l == 0 ? prec_dst : (int)CHEBFD_PREC_FP64, l == 0 ? ld_dst : (int64_t)PW);
         CHEBFD_HIP(hipGetLastError());
     }
