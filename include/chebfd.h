@@ -164,8 +164,9 @@ int chebfd_random_phase(const chebfd_matrix *H, int32_t m, int32_t n_b, int32_t 
  * d_xy (blocked layout, n_s vectors, precision `prec`) holds X on entry and
  * Y = sum_{p=0}^{n_p} gamma_p T_p(alpha H + beta I) X on return (the paper
  * overwrites X by the filtered block).  Each step p >= 3 is one launch of the
- * fused kernel (chebfd_op: recurrence W <- 2(alpha H + beta I) U - W, the dot
- * products eta_p = <W, U>, mu_p = <U, U> and X <- X + gamma_p W in one pass).
+ * fused kernel (chebfd_op: recurrence W <- 2(alpha H + beta I) U - W and the dot
+ * products eta_p = <W, U>, mu_p = <U, U> in one pass over the rows; every third
+ * launch also adds the terms of the last three steps to X, in order of p).
  * d_u, d_w: n x n_b work blocks of the same precision.
  * d_eta: (n_p + 1) x n_s c128 and d_nu: (n_p + 1) x n_s FP64 (entry p*n_s + j,
  * column j in 0..n_s-1), receiving for p = 1..n_p

@@ -22,6 +22,15 @@ def step_bytes(n: int, nnz: int, n_b: int, prec: int) -> tuple[int, int]:
     return read, write
 
 
+def launch_bytes(n: int, nnz: int, n_b: int, prec: int) -> tuple[float, float]:
+    """(read, write) bytes that one recurrence launch of the fused filter moves at least, averaged
+    over three: the matrix, U and W read and W written by each, and X read and written by every
+    third, which adds the terms of three steps (T_{k-2}, T_{k-1} and T_k are all at hand there)."""
+    s = value_bytes(prec)
+    block = n * n_b * s
+    return nnz * (s + 4) + (2 + 1 / 3) * block, (1 + 1 / 3) * block
+
+
 def start_bytes(n: int, nnz: int, n_b: int, prec: int) -> tuple[int, int]:
     """(read, write) of the two start launches (the start of Alg. 1): U = H~X; W = 2H~U - X, X = ..."""
     s = value_bytes(prec)
