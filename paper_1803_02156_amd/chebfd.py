@@ -319,7 +319,9 @@ def chebfd_update(a: torch.Tensor, M: torch.Tensor, prec_z: int | None = None):
     prec_a = PREC_FP64 if a.dtype == torch.complex128 else PREC_MIXED
     prec_z = prec_a if prec_z is None else prec_z
     Mc = M.to(torch.complex128).T.contiguous()      # column-major
-    z = torch.zeros(((m2 + n_b - 1) // n_b, n, n_b), dtype=vec_dtype(prec_z), device=a.device)
+    # only the padding columns of a last, partial block are not written by the call
+    alloc = torch.empty if m2 % n_b == 0 else torch.zeros
+    z = alloc(((m2 + n_b - 1) // n_b, n, n_b), dtype=vec_dtype(prec_z), device=a.device)
     check(load().chebfd_update(n, n_b, m1, m2, prec_a, _ptr(a), _ptr(Mc), m1, prec_z, _ptr(z), _stream()))
     return z
 
@@ -334,7 +336,8 @@ def chebfd_tsqr(y: torch.Tensor, m: int | None = None):
     sz = ctypes.c_size_t()
     check(load().chebfd_tsqr_query(n, m, n_b, ctypes.byref(sz)))
     work = device_buffer(sz.value, y.device)
-    q = torch.zeros_like(y)
+    # columns past m are not written by the call
+    q = torch.empty_like(y) if m == nblk * n_b else torch.zeros_like(y)
     R = torch.zeros((m, m), dtype=torch.complex128, device=y.device)   # column-major m x m
     check(load().chebfd_tsqr(n, m, n_b, prec, _ptr(y), _ptr(q), _ptr(R), m, _ptr(work), sz.value, _stream()))
     return q, R.T
