@@ -54,9 +54,12 @@ int device_props(DeviceProps *out) {
 }
 
 // Static scratch of chebfd_filter_noalloc: the partial dot-product sums the step
-// kernels pass from one launch to the next.  Each device holds its own copy
-// until the process ends.  Host code never uses the array's name as a device
-// address: scratch_ptr() looks the copy of the current device up once.
+// kernels pass from one launch to the next and the window kernel's progress
+// words.  No block of the search space is ever kept in it: it is shared by all
+// calls on a device, so calls that overlap may spoil each other's moments but not
+// the filtered blocks.  Each device holds its own copy until the process ends.
+// Host code never uses the array's name as a device address: scratch_ptr() looks
+// the copy of the current device up once.
 constexpr size_t kNoAllocScratchBytes = size_t(4) << 20;
 __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
@@ -677,9 +680,11 @@ int chebfd_filter_noalloc(const chebfd_matrix *H, double alpha, double beta, con
                     n_b, need, kNoAllocScratchBytes);
     void *work = nullptr;
     if ((rc = scratch_ptr(&work))) return rc;
+    // exactly what one block needs: the room for several blocks per launch would hold their
+    // U and W in the shared array
     size_t need2 = 0;
     if ((rc = check_filter_args(H, alpha, beta, h_gamma, n_p, n_s, n_b, prec, d_xy, d_u, d_w, d_eta, d_nu, work,
-                                kNoAllocScratchBytes, &geo, &need2)))
+                                need, &geo, &need2)))
         return rc;
     return filter_run(H, alpha, beta, h_gamma, n_p, n_s, n_b, prec, d_xy, d_u, d_w, d_eta, d_nu, work, need2, geo,
                       false, static_cast<hipStream_t>(stream));
