@@ -174,16 +174,18 @@ int chebfd_random_phase(const chebfd_matrix *H, int32_t m, int32_t n_b, int32_t 
  * (with <a, b> = sum_i conj(a_i) b_i, FP64 accumulation, deterministic
  * summation order); row 0 is not written.  May be NULL together (moments not
  * needed is not faster: they are computed in the same pass).
- * d_work: chebfd_filter_query bytes (the partial sums of the dot products,
- * one progress word per workgroup of the window kernel, tagged per launch, so
- * nothing has to start at zero, and for small matrices the U and W blocks of up
- * to 7 further blocks of the search space, at most 16 MB with their partial sums
- * beside them, which are then stepped by one launch; the results do not depend on
- * it).  n_b in {1,2,4,8,16,32,64,128},
+ * d_work: at least chebfd_filter_query bytes (the partial sums of the dot
+ * products and one progress word per workgroup of the window kernel, tagged per
+ * launch, so nothing has to start at zero).  With chebfd_filter_query_blocks
+ * bytes, which for a small matrix and n_s > n_b hold the U, W and partial sums
+ * of up to 7 further blocks too, one launch steps up to 8 blocks of the search
+ * space; the filtered blocks and moments are the same bits either way.  That
+ * size for some n_s also serves every smaller n_s.  n_b in {1,2,4,8,16,32,64,128},
  * n_s % n_b == 0, n_p >= 0, gamma[n_p + 1] on the host.
  * Buffers must be 256-byte aligned and must not overlap.
  */
 int chebfd_filter_query(const chebfd_matrix *H, int32_t n_b, size_t *work_bytes);
+int chebfd_filter_query_blocks(const chebfd_matrix *H, int32_t n_s, int32_t n_b, size_t *work_bytes);
 
 /*
  * The fused-step kernel that chebfd_filter, chebfd_op, chebfd_spmmv and the

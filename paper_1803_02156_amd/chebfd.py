@@ -176,6 +176,12 @@ def chebfd_filter_query(H: Matrix, n_b: int) -> int:
     return b.value
 
 
+def chebfd_filter_query_blocks(H: Matrix, n_s: int, n_b: int) -> int:
+    b = ctypes.c_size_t()
+    check(load().chebfd_filter_query_blocks(H.ref(), n_s, n_b, ctypes.byref(b)))
+    return b.value
+
+
 class FilterWork:
     """Work buffers of chebfd_filter for one (matrix, n_b, n_p, n_s): U, W, partials, moments."""
 
@@ -184,7 +190,7 @@ class FilterWork:
         dev = H.buf.device
         self.u = torch.empty((H.n, n_b), dtype=dt, device=dev)
         self.w = torch.empty((H.n, n_b), dtype=dt, device=dev)
-        self.nbytes = chebfd_filter_query(H, n_b)
+        self.nbytes = chebfd_filter_query_blocks(H, n_s, n_b)
         self.work = device_buffer(self.nbytes, dev)
         self.eta = torch.zeros((n_p + 1, n_s), dtype=torch.complex128, device=dev) if moments else None
         self.nu = torch.zeros((n_p + 1, n_s), dtype=torch.float64, device=dev) if moments else None

@@ -527,24 +527,28 @@ static int filter_geometry(const chebfd_matrix *H, int prec, int nb, StepGeometr
     return CHEBFD_OK;
 }
 
-// Small matrices: further workspace that lets one launch step up to small.batch
-// blocks of the search space (the U and W of all but the first and the partial sums
-// of all), after the part that one block needs.  A workspace without it is taken too, block by block.
+// Small matrices: further workspace that lets one launch step k = min(small.batch,
+// nblocks) of the search space's nblocks blocks (the U and W of all but the first and
+// the partial sums of all), after the part that one block needs.  A workspace without
+// it is taken too, block by block.  Grows with nblocks: the room for a search space
+// serves every smaller one.
 struct BatchLayout {
+    int k;
     size_t part, u, w, total;   // offsets of the second partial buffer, U and W
 };
-static BatchLayout batch_layout(const chebfd_matrix *H, int prec, int nb, const StepGeometry &g) {
-    BatchLayout L{0, 0, 0, 0};
-    if (!g.wave || g.small.batch < 2) return L;
-    const size_t k = g.small.batch, blocks = round_up((k - 1) * vec_elem_bytes(prec) * (size_t)H->n * nb, 256);
-    L.part = filter_part_bytes(nb, g.G * g.small.batch);
+static BatchLayout batch_layout(const chebfd_matrix *H, int prec, int nb, const StepGeometry &g, int nblocks) {
+    BatchLayout L{1, 0, 0, 0, 0};
+    if (!g.wave || std::min(g.small.batch, nblocks) < 2) return L;
+    L.k = std::min(g.small.batch, nblocks);
+    const size_t blocks = round_up((size_t)(L.k - 1) * vec_elem_bytes(prec) * (size_t)H->n * nb, 256);
+    L.part = filter_part_bytes(nb, g.G * L.k);
     L.u = 2 * L.part;
     L.w = L.u + blocks;
     L.total = L.w + blocks;
     return L;
 }
-static size_t batch_bytes(const chebfd_matrix *H, int prec, int nb, const StepGeometry &g) {
-    return batch_layout(H, prec, nb, g).total;
+static size_t batch_bytes(const chebfd_matrix *H, int prec, int nb, const StepGeometry &g, int nblocks) {
+    return batch_layout(H, prec, nb, g, nblocks).total;
 }
 
 static int launch_any(const chebfd_matrix *H, int prec, int nb, int mode, StepArgs a,
@@ -564,7 +568,19 @@ int chebfd_filter_query(const chebfd_matrix *H, int32_t n_b, size_t *work_bytes)
     CHEBFD_REQUIRE(work_bytes != nullptr, "work_bytes is NULL");
     StepGeometry g;
     if ((rc = filter_geometry(H, H->prec, n_b, &g))) return rc;
-    *work_bytes = filter_work_bytes(n_b, g.G) + batch_bytes(H, H->prec, n_b, g);
+    *work_bytes = filter_work_bytes(n_b, g.G);
+    return CHEBFD_OK;
+}
+
+int chebfd_filter_query_blocks(const chebfd_matrix *H, int32_t n_s, int32_t n_b, size_t *work_bytes) {
+    clear_error();
+    int rc;
+    if ((rc = check_handle(H)) || (rc = check_prec_nb(H->prec, n_b))) return rc;
+    CHEBFD_REQUIRE(n_s >= 1 && n_s % n_b == 0, "n_s = %d must be a positive multiple of n_b = %d", n_s, n_b);
+    CHEBFD_REQUIRE(work_bytes != nullptr, "work_bytes is NULL");
+    StepGeometry g;
+    if ((rc = filter_geometry(H, H->prec, n_b, &g))) return rc;
+    *work_bytes = filter_work_bytes(n_b, g.G) + batch_bytes(H, H->prec, n_b, g, n_s / n_b);
     return CHEBFD_OK;
 }
 
@@ -636,7 +652,7 @@ static int check_filter_args(const chebfd_matrix *H, double alpha, double beta, 
         CHEBFD_REQUIRE(!overlap(d_eta, 2 * mb, d_nu, mb), "d_eta and d_nu overlap");
     }
     // several blocks per launch where the workspace has room for them beside everything else
-    const size_t more = n_s > n_b ? batch_bytes(H, prec, n_b, *geo) : 0;
+    const size_t more = batch_bytes(H, prec, n_b, *geo, n_s / n_b);
     const size_t mom = sizeof(double) * (size_t)(n_p + 1) * n_s;
     const bool room = more > 0 && work_bytes >= need + more && !overlap(d_work, need + more, d_xy, xy_bytes) &&
                       !overlap(d_work, need + more, d_u, blk) && !overlap(d_work, need + more, d_w, blk) &&
@@ -793,9 +809,9 @@ static int filter_run(const chebfd_matrix *H, double alpha, double beta, const d
     // are more and the workspace has room for their U and W
     int batch = 1;
     char *more_u = nullptr, *more_w = nullptr;
-    const BatchLayout bl = batch_layout(H, prec, n_b, geo);
-    if (bl.total > 0 && nblocks > 1 && work_bytes >= filter_work_bytes(n_b, G) + bl.total) {
-        batch = geo.small.batch;
+    const BatchLayout bl = batch_layout(H, prec, n_b, geo, nblocks);
+    if (bl.k > 1 && work_bytes >= filter_work_bytes(n_b, G) + bl.total) {
+        batch = bl.k;
         char *base = static_cast<char *>(d_work) + filter_work_bytes(n_b, G);
         part[0] = reinterpret_cast<double *>(base);
         part[1] = reinterpret_cast<double *>(base + bl.part);
@@ -939,7 +955,7 @@ static int kpm_layout(const chebfd_matrix *H, int n_steps, int R, StepGeometry *
                    "R = %d must be a power of two up to 32 or a multiple of 32", R);
     const int n_b = R < 32 ? R : 32;
     if ((rc = filter_geometry(H, H->prec, n_b, geo))) return rc;
-    L->filter_bytes = filter_work_bytes(n_b, geo->G) + (R > n_b ? batch_bytes(H, H->prec, n_b, *geo) : 0);
+    L->filter_bytes = filter_work_bytes(n_b, geo->G) + batch_bytes(H, H->prec, n_b, *geo, R / n_b);
     const size_t sw = vec_elem_bytes(H->prec), n = H->n;
     size_t at = 0;
     auto take = [&](size_t b) { size_t h = at; at = round_up(at + b, 256); return h; };

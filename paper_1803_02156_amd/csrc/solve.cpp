@@ -45,14 +45,14 @@ int solve_layout(const chebfd_matrix *H, const chebfd_matrix *H64, const chebfd_
                  SolveLayout *L) {
     const size_t n = H->n, ns = p->n_s, nb = p->n_b, sw = vec_elem_bytes(p->prec);
     size_t f1 = 0, f2 = 0;
-    int rc = chebfd_filter_query(H, p->n_b, &f1);
+    int rc = chebfd_filter_query_blocks(H, p->n_s, p->n_b, &f1);
     if (rc) return rc;
-    if ((rc = chebfd_filter_query(H64, p->n_b, &f2))) return rc;
+    if ((rc = chebfd_filter_query(H64, p->n_b, &f2))) return rc;   // products with one block
     L->fwork_bytes = std::max(f1, f2);
     if (p->prec != CHEBFD_PREC_FP64 && p->n_b > 1) {
-        // the FP64 stage of a mixed run filters with n_b / 2
+        // the FP64 stage of a mixed run filters at most n_s / 2 vectors with n_b / 2
         size_t f3 = 0;
-        if ((rc = chebfd_filter_query(H64, p->n_b / 2, &f3))) return rc;
+        if ((rc = chebfd_filter_query_blocks(H64, p->n_s / 2, p->n_b / 2, &f3))) return rc;
         L->fwork_bytes = std::max(L->fwork_bytes, f3);
     }
     // the largest partial buffer of any Gram product the iteration forms (SVQB:
