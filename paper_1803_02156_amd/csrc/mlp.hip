@@ -405,7 +405,9 @@ size_t mlp_work_layout(int batch, char *base, MlpWork *w) {
 }
 
 // The forward pass takes the rows kernel up to this batch and layer-wise GEMMs past it
-// (16000 rows: 79 and 102 us; 32000: 154 and 122)
+// (16000 rows: 79 and 102 us; 32000: 154 and 122).  Outputs that lie inside the features
+// or the parameters take the GEMMs too: their first launches have read these before the
+// last one writes, while in the rows kernel other workgroups still read them.
 constexpr int kRowsMax = 16384;
 
 int check_batch(int batch, const void *d_work, size_t work_bytes, size_t *need) {
@@ -434,7 +436,10 @@ int launch_rows(const MlpRows &a, hipStream_t s) {
 
 int forward(const float *P, int batch, const float *X, float *Y, const MlpWork &w, hipStream_t s) {
     int rc;
-    if (batch <= kRowsMax) {
+    const size_t ybytes = sizeof(float) * kOut * (size_t)batch;
+    const bool apart = !overlap(Y, ybytes, X, sizeof(float) * kIn * (size_t)batch) &&
+                       !overlap(Y, ybytes, P, sizeof(float) * kParams);
+    if (batch <= kRowsMax && apart) {
         MlpRows a{};
         a.P = P;
         a.X = X;
