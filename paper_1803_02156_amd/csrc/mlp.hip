@@ -275,15 +275,17 @@ __global__ __launch_bounds__(kRowT) void mlp_rows_kernel(MlpRows a) {
 // layer inputs A of every row: g[i][k] = sum_b D[b][i] A[b][k], the bias as the
 // column k = K with A = 1.  A workgroup forms a 32 x 32 tile, its 16 waves every
 // sixteenth batch row each (4 x 4 entries per lane), summed in wave order; one more
-// workgroup sums the loss.
+// workgroup sums the loss.  `first`: index of the launch's first workgroup (the loss can
+// go ahead of the gradients in a launch of its own).
 constexpr int kWT = 32, kWWaves = kRowT / 64;
 constexpr int kWk1 = (kIn + 1 + kWT - 1) / kWT, kWk2 = (kHid + 1 + kWT - 1) / kWT, kWi = kHid / kWT;
 constexpr int kWTiles1 = kWi * kWk1, kWTiles2 = kWi * kWk2, kWTiles = kWTiles1 + kWTiles2 + kWk2;
 
-__global__ __launch_bounds__(kRowT) void mlp_wgrad_kernel(MlpRows a, float *__restrict__ G, float *__restrict__ loss) {
+__global__ __launch_bounds__(kRowT) void mlp_wgrad_kernel(MlpRows a, float *__restrict__ G, float *__restrict__ loss, int first) {
     __shared__ float sred[kWWaves][kWT][kWT + 1];
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-    if (blockIdx.x == kWTiles) {
+    const int t = static_cast<int>(blockIdx.x) + first;
+    if (t == kWTiles) {
         float s = 0.0f;
         for (int b = tid; b < a.batch; b += kRowT) s += a.lossrow[b];
         float *f = &sred[0][0][0];
@@ -299,7 +301,6 @@ __global__ __launch_bounds__(kRowT) void mlp_wgrad_kernel(MlpRows a, float *__re
     const float *D, *A;
     float *gw, *gb;
     int ldd, lda, N, K, it, kt;
-    const int t = blockIdx.x;
     if (t < kWTiles1) {
         D = a.dz1; A = a.X; ldd = kHid; lda = kIn; N = kHid; K = kIn;
         gw = G + kOffW1; gb = G + kOffB1; it = t / kWk1; kt = t % kWk1;
@@ -506,7 +507,13 @@ int chebfd_mlp_grad(const float *d_params, int32_t batch, const float *d_x, cons
     a.inv_b = 1.0f / (float)batch;
     a.batch = batch;
     if ((rc = launch_rows<true>(a, s))) return rc;
-    hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(kWTiles + 1), dim3(kRowT), 0, s, a, d_grad, d_loss);
+    // a loss that lies inside the gradient is written first, so that the gradient is whole
+    const bool apart = !overlap(d_loss, sizeof(float), d_grad, sizeof(float) * kParams);
+    if (!apart) {
+        hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(1), dim3(kRowT), 0, s, a, d_grad, d_loss, kWTiles);
+        CHEBFD_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(apart ? kWTiles + 1 : kWTiles), dim3(kRowT), 0, s, a, d_grad, d_loss, 0);
     CHEBFD_HIP(hipGetLastError());
     return CHEBFD_OK;
 }

@@ -1,7 +1,8 @@
 """Network calls whose buffers lie inside one another: the outputs of the forward pass
 inside the features or the first layers' parameters (both are read before the last
 layer writes), against the FP64 oracle (1e-4 relative: sums of 258 products in FP32 err
-by at most 258 2^-24 = 1.6e-5)."""
+by at most 258 2^-24 = 1.6e-5); the loss inside the gradient or the targets (the gradient
+is whole, the same bits as with a loss of its own)."""
 import ctypes
 
 import numpy as np
@@ -55,3 +56,29 @@ def test_forward_outputs_inside_inputs(P, B, where):
         P.check(P.load().chebfd_mlp_forward(_ptr(p), B, _ptr(x), _ptr(into, at), _ptr(work), nbytes, P.chebfd._stream()))
         y = into[at:at + ref.size].view(B, OM.D_OUT).cpu().numpy()
         assert np.max(np.abs(y - ref)) <= 1e-4 * max(1.0, np.max(np.abs(ref)))
+
+
+@pytest.mark.parametrize("B", [1, 125, 1027])
+@pytest.mark.parametrize("at", [0, 33023, 33024, 49920, 49921])
+def test_loss_inside_gradient(P, B, at):
+    theta, X, T = _inputs(B)
+    p, x, t = (torch.from_numpy(v).cuda() for v in (theta, X, T))
+    _, ref = P.chebfd_mlp_grad(p, x, t)
+    work, nbytes = _work(P, B)
+    for _ in range(3):
+        g = torch.full_like(ref, float("nan"))
+        P.check(P.load().chebfd_mlp_grad(_ptr(p), B, _ptr(x), _ptr(t), _ptr(g, at), _ptr(g), _ptr(work), nbytes,
+                                         P.chebfd._stream()))
+        assert torch.equal(g, ref)
+
+
+@pytest.mark.parametrize("B", [1, 125, 1027])
+def test_loss_inside_targets(P, B):
+    theta, X, T = _inputs(B)
+    p, x, t = (torch.from_numpy(v).cuda() for v in (theta, X, T))
+    loss, ref = P.chebfd_mlp_grad(p, x, t)
+    work, nbytes = _work(P, B)
+    g = torch.full_like(ref, float("nan"))
+    P.check(P.load().chebfd_mlp_grad(_ptr(p), B, _ptr(x), _ptr(t), _ptr(t, 2 * B - 1), _ptr(g), _ptr(work), nbytes,
+                                     P.chebfd._stream()))
+    assert torch.equal(g, ref) and t.view(-1)[2 * B - 1] == loss[0]
