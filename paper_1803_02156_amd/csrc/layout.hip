@@ -3,6 +3,7 @@
 // Gershgorin bound reduction and the HBM stream probe.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -58,42 +59,48 @@ __global__ __launch_bounds__(kT) void pack_kernel(const int32_t *__restrict__ pe
 // Bound: HBM.  524288 x 64 c64 unpack: 859 -> 153 us, pack 396 -> 192 (element by
 // element the column-major side was touched 16 bytes at a time with stride n).
 constexpr int kPackRows = 64;
+// Row tiles per launch column; more rows (67 million) go through the loop, since a grid
+// holds at most 2^32 - 1 work-items in x.
+constexpr int64_t kPackMaxGrid = 1 << 20;
 template <typename T, bool UNPACK, int CB>
 __global__ __launch_bounds__(kT) void pack_tile_kernel(const int32_t *__restrict__ perm, int64_t n, int nb,
                                                        const void *src, void *dst) {
     using VT = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
     __shared__ VT tile[kPackRows][CB + 1];
-    const int64_t i0 = (int64_t)blockIdx.x * kPackRows;
     const int64_t c0 = (int64_t)blockIdx.y * CB;                 // first column
     const int64_t bbase = c0 / nb * n * nb + c0 % nb;            // blocked index of (row 0, column c0)
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     constexpr int RPP = kT / CB;                                 // rows per pass, blocked side
     const int c = threadIdx.x % CB, r0 = threadIdx.x / CB;
-    const int64_t il = i0 + lane;
-    const int64_t row = il < n ? (perm ? perm[il] : il) : 0;     // this lane's row, column-major side
-    if constexpr (UNPACK) {
+    const int64_t stride = (int64_t)gridDim.x * kPackRows;
+    for (int64_t i0 = (int64_t)blockIdx.x * kPackRows; i0 < n; i0 += stride) {
+        const int64_t il = i0 + lane;
+        const int64_t row = il < n ? (perm ? perm[il] : il) : 0;     // this lane's row, column-major side
+        if constexpr (UNPACK) {
 #pragma unroll
-        for (int r = r0; r < kPackRows; r += RPP)
-            if (i0 + r < n) tile[r][c] = static_cast<const VT *>(src)[bbase + (i0 + r) * nb + c];
-        __syncthreads();
-        for (int k = wv; k < CB; k += kT / 64)
-            if (il < n) {
-                const VT v = tile[lane][k];
-                static_cast<double2 *>(dst)[(c0 + k) * n + row] = double2{(double)v.x, (double)v.y};
-            }
-    } else {
-        for (int k = wv; k < CB; k += kT / 64)
-            if (il < n) {
-                const double2 v = static_cast<const double2 *>(src)[(c0 + k) * n + row];
-                VT f;
-                f.x = static_cast<T>(v.x);
-                f.y = static_cast<T>(v.y);
-                tile[lane][k] = f;
-            }
-        __syncthreads();
+            for (int r = r0; r < kPackRows; r += RPP)
+                if (i0 + r < n) tile[r][c] = static_cast<const VT *>(src)[bbase + (i0 + r) * nb + c];
+            __syncthreads();
+            for (int k = wv; k < CB; k += kT / 64)
+                if (il < n) {
+                    const VT v = tile[lane][k];
+                    static_cast<double2 *>(dst)[(c0 + k) * n + row] = double2{(double)v.x, (double)v.y};
+                }
+        } else {
+            for (int k = wv; k < CB; k += kT / 64)
+                if (il < n) {
+                    const double2 v = static_cast<const double2 *>(src)[(c0 + k) * n + row];
+                    VT f;
+                    f.x = static_cast<T>(v.x);
+                    f.y = static_cast<T>(v.y);
+                    tile[lane][k] = f;
+                }
+            __syncthreads();
 #pragma unroll
-        for (int r = r0; r < kPackRows; r += RPP)
-            if (i0 + r < n) static_cast<VT *>(dst)[bbase + (i0 + r) * nb + c] = tile[r][c];
+            for (int r = r0; r < kPackRows; r += RPP)
+                if (i0 + r < n) static_cast<VT *>(dst)[bbase + (i0 + r) * nb + c] = tile[r][c];
+        }
+        if (i0 + stride < n) __syncthreads();   // the tile is written again
     }
 }
 
@@ -101,7 +108,7 @@ template <typename T, bool UNPACK>
 static void launch_pack_tile(const int32_t *perm, int64_t n, int m, int nb, const void *src, void *dst,
                              hipStream_t s) {
     const int cb = nb < 32 ? nb : 32;
-    const dim3 grid(static_cast<unsigned>((n + kPackRows - 1) / kPackRows), m / cb);
+    const dim3 grid(static_cast<unsigned>(std::min((n + kPackRows - 1) / kPackRows, kPackMaxGrid)), m / cb);
     switch (cb) {
         case 4: hipLaunchKernelGGL((pack_tile_kernel<T, UNPACK, 4>), grid, dim3(kT), 0, s, perm, n, nb, src, dst); break;
         case 8: hipLaunchKernelGGL((pack_tile_kernel<T, UNPACK, 8>), grid, dim3(kT), 0, s, perm, n, nb, src, dst); break;
