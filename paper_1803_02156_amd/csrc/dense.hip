@@ -300,46 +300,55 @@ __global__ __launch_bounds__(kT) void gram_kernel(const void *A, int nb_a, const
 // Hermitian product: the tiles on the diagonal first (nsplit_d splits each), then
 // the ntiles - tiles_a above it; entries above the diagonal also give their mirror
 // image S(b, a) = conj S(a, b).
+// per_tile workgroups a tile (its first columns, where it is narrow); more than
+// kReduceMaxGrid (32768 tiles) go through the loop, since a grid holds at most 2^32 - 1
+// work-items.
 constexpr int kRE = 32, kRS = kT / kRE;
+constexpr int64_t kReduceMaxGrid = 1 << 22;
 __global__ __launch_bounds__(kT) void gram_reduce_kernel(const double *part, int nsplit, int nsplit_d, int ntiles,
-                                                         int tiles_a, int herm, int m1, int m2, double *S,
-                                                         int ld) {
+                                                         int per_tile, int tiles_a, int herm, int m1, int m2,
+                                                         double *S, int ld) {
     __shared__ double2 sred[kRS][kRE];
-    const double2 *p = reinterpret_cast<const double2 *>(part);
     const int el = threadIdx.x % kRE, sl = threadIdx.x / kRE;
-    const int per_tile = gridDim.x / ntiles;   // workgroups per tile (its first columns, where it is narrow)
-    int tile = blockIdx.x / per_tile, set = ntiles, splits = nsplit;
-    const int e = blockIdx.x % per_tile * kRE + el;
-    int ta = tile, tb = tile;
-    if (!herm) {
-        gram_tile(tile, tiles_a, false, &ta, &tb);
-    } else if (tile < tiles_a) {
-        set = tiles_a;
-        splits = nsplit_d;
-    } else {
-        tile -= tiles_a;
-        set = ntiles - tiles_a;
-        p += (int64_t)nsplit_d * tiles_a * (kGT * kGT);
-        gram_tile(tile, tiles_a, true, &ta, &tb);
-    }
-    double sr = 0.0, si = 0.0;
+    const int64_t total = (int64_t)ntiles * per_tile;
+    for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
+        const double2 *p = reinterpret_cast<const double2 *>(part);
+        int tile = static_cast<int>(w / per_tile), set = ntiles, splits = nsplit;
+        const int e = static_cast<int>(w % per_tile) * kRE + el;
+        int ta = tile, tb = tile;
+        if (!herm) {
+            gram_tile(tile, tiles_a, false, &ta, &tb);
+        } else if (tile < tiles_a) {
+            set = tiles_a;
+            splits = nsplit_d;
+        } else {
+            tile -= tiles_a;
+            set = ntiles - tiles_a;
+            p += (int64_t)nsplit_d * tiles_a * (kGT * kGT);
+            gram_tile(tile, tiles_a, true, &ta, &tb);
+        }
+        double sr = 0.0, si = 0.0;
 #pragma unroll 8
-    for (int s = sl; s < splits; s += kRS) {
-        const double2 v = p[((int64_t)s * set + tile) * (kGT * kGT) + e];
-        sr += v.x;
-        si += v.y;
+        for (int s = sl; s < splits; s += kRS) {
+            const double2 v = p[((int64_t)s * set + tile) * (kGT * kGT) + e];
+            sr += v.x;
+            si += v.y;
+        }
+        sred[sl][el] = double2{sr, si};
+        __syncthreads();
+        if (sl == 0) {
+            for (int q = 1; q < kRS; ++q) {
+                sr += sred[q][el].x;
+                si += sred[q][el].y;
+            }
+            const int a = ta * kGT + e % kGT, b = tb * kGT + e / kGT;
+            if (a < m1 && b < m2 && !(herm && a > b)) {
+                reinterpret_cast<double2 *>(S)[(int64_t)b * ld + a] = double2{sr, si};
+                if (herm && a != b) reinterpret_cast<double2 *>(S)[(int64_t)a * ld + b] = double2{sr, -si};
+            }
+        }
+        if (w + gridDim.x < total) __syncthreads();   // sred is written again
     }
-    sred[sl][el] = double2{sr, si};
-    __syncthreads();
-    if (sl > 0) return;
-    for (int q = 1; q < kRS; ++q) {
-        sr += sred[q][el].x;
-        si += sred[q][el].y;
-    }
-    const int a = ta * kGT + e % kGT, b = tb * kGT + e / kGT;
-    if (a >= m1 || b >= m2 || (herm && a > b)) return;
-    reinterpret_cast<double2 *>(S)[(int64_t)b * ld + a] = double2{sr, si};
-    if (herm && a != b) reinterpret_cast<double2 *>(S)[(int64_t)a * ld + b] = double2{sr, -si};
 }
 
 // ---------------------------------------------------------------------------
@@ -1117,8 +1126,10 @@ int launch_gram(const void *A, int prec_a, int nb_a, const void *B, int prec_b, 
 #undef CHEBFD_GRAM_ONE
     CHEBFD_HIP(hipGetLastError());
     const int all = herm ? ta + ntiles : ntiles;
-    const int G = all * (kGT * (narrow ? 32 : kGT) / kRE);
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(G), dim3(kT), 0, s, part, ks, kd, all, ta, herm, m1, m2, S, ld);
+    const int per_tile = kGT * (narrow ? 32 : kGT) / kRE;
+    const unsigned G = static_cast<unsigned>(std::min((int64_t)all * per_tile, kReduceMaxGrid));
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3(G), dim3(kT), 0, s, part, ks, kd, all, per_tile, ta, herm, m1, m2, S,
+                       ld);
     CHEBFD_HIP(hipGetLastError());
     return CHEBFD_OK;
 }
