@@ -482,10 +482,10 @@ static int64_t *filter_prog(void *d_work, int nb, int G) {
 
 // Launch geometry of the step kernels.  The window kernel (U staged in LDS)
 // serves the block widths it has instances for when the row order keeps most
-// gathers within its window; otherwise the LDS-staged kernel (matrix slots in
-// LDS) is used for chunks of C = 32 rows with rows of at most 16 entries (its
-// instances' tile width); otherwise n_b >= 32 uses the row-per-wavefront
-// kernel and smaller n_b the multi-row kernel.
+// gathers within its window; otherwise chunks of at most 32 rows with rows of at
+// most 16 entries take the small-matrix kernel (up to a size, n_b = 1 at every
+// size) or the LDS-staged kernel (matrix slots of a tile in LDS); otherwise
+// n_b >= 32 uses the row-per-wavefront kernel and smaller n_b the multi-row kernel.
 struct StepGeometry {
     int kind;           // 0 = LDS-staged, 1 = row per wavefront, 2 = multi-row, 3 = window
     int64_t npass;      // passes (kinds 1, 2)
@@ -505,11 +505,15 @@ static int filter_geometry(const chebfd_matrix *H, int prec, int nb, StepGeometr
         g->kind = 3;
         g->npass = g->win.ntiles;
         g->G = g->win.G;
+    } else if (wave_geometry(H, prec, nb, &g->small)) {
+        g->kind = 0;
+        g->wave = true;
+        g->npass = g->small.npass;
+        g->G = g->small.G;
     } else if (lds_geometry(H, prec, nb, d.num_cus, &g->lds)) {
         g->kind = 0;
-        g->wave = wave_geometry(H, prec, nb, &g->small);
-        g->npass = g->wave ? g->small.npass : g->lds.ntiles;
-        g->G = g->wave ? g->small.G : g->lds.G;
+        g->npass = g->lds.ntiles;
+        g->G = g->lds.G;
     } else if (nb >= kRowKernelMinNb) {
         g->kind = 1;
         const int rows = row_kernel_rows_per_pass(nb);

@@ -375,10 +375,10 @@ int launch_lds_w(int mode, const StepArgs &a, const LdsGeometry &g, hipStream_t 
     return launch_lds_mode<T, NB, kMaxTileWidth>(mode, a, g, s);
 }
 
+// (n_b = 1 takes the small-matrix kernel at every size)
 template <typename T>
 int launch_lds_nb(int nb, int mode, const StepArgs &a, const LdsGeometry &g, hipStream_t s) {
     switch (nb) {
-        case 1: return launch_lds_w<T, 1>(mode, a, g, s);
         case 2: return launch_lds_w<T, 2>(mode, a, g, s);
         case 4: return launch_lds_w<T, 4>(mode, a, g, s);
         case 8: return launch_lds_w<T, 8>(mode, a, g, s);
@@ -404,7 +404,6 @@ int occ_lds(int maxw, size_t lds) {
 template <typename T>
 int occ_lds_nb(int nb, int maxw, size_t lds) {
     switch (nb) {
-        case 1: return occ_lds<T, 1>(maxw, lds);
         case 2: return occ_lds<T, 2>(maxw, lds);
         case 4: return occ_lds<T, 4>(maxw, lds);
         case 8: return occ_lds<T, 8>(maxw, lds);

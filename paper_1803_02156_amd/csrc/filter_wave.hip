@@ -373,7 +373,7 @@ int launch_wave_nb(int nb, int mode, const StepArgs &a, const WaveGeometry &g, h
 }  // namespace
 
 bool wave_geometry(const chebfd_matrix *H, int prec, int nb, WaveGeometry *g) {
-    if (H->max_width > kWaveMaxWidth) return false;
+    if (H->max_width > kWaveMaxWidth || H->C > 32) return false;   // the LDS-staged kernel's shapes
     const int64_t block = (int64_t)vec_elem_bytes(prec) * H->n * nb;
     if (nb > 1 && 3 * block > kWaveMaxBytes) return false;
     const int cpl = (prec == CHEBFD_PREC_MIXED && nb >= 2) ? 2 : 1;   // cols_per_lane<T, NB>()
