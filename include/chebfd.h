@@ -199,9 +199,10 @@ int chebfd_filter_query_blocks(const chebfd_matrix *H, int32_t n_s, int32_t n_b,
  *                          ranges of one XCD are held within a few tiles of
  *                          each other through progress words in the workspace
  *   CHEBFD_KERNEL_LDS      the tile's matrix slots staged in LDS, U gathered from
- *                          memory (rows of up to 16 entries, C <= 32; small
- *                          matrices by a variant in which each wavefront stages
- *                          its own rows' slots)
+ *                          memory (rows of up to 16 entries, C <= 32); matrices
+ *                          whose U, W and Y blocks take at most 210 MB together,
+ *                          and n_b = 1, by a variant in which each wavefront stages
+ *                          its own rows' slots (chebfd_step_kernel_small: 1)
  *   CHEBFD_KERNEL_ROW      one row per wavefront group (n_b >= 32, wider rows)
  *   CHEBFD_KERNEL_MULTIROW several rows per wavefront (n_b < 32, wider rows)
  */
@@ -210,6 +211,7 @@ int chebfd_filter_query_blocks(const chebfd_matrix *H, int32_t n_s, int32_t n_b,
 #define CHEBFD_KERNEL_MULTIROW 2
 #define CHEBFD_KERNEL_WINDOW   3
 int chebfd_step_kernel(const chebfd_matrix *H, int32_t n_b, int32_t *kind);
+int chebfd_step_kernel_small(const chebfd_matrix *H, int32_t n_b, int32_t *small);
 int chebfd_filter(const chebfd_matrix *H, double alpha, double beta, const double *h_gamma,
                   int32_t n_p, int32_t n_s, int32_t n_b, int32_t prec, void *d_xy, void *d_u,
                   void *d_w, double *d_eta, double *d_nu, void *d_work, size_t work_bytes,

@@ -71,6 +71,7 @@ SIGNATURES = {
     "chebfd_filter_query": (ctypes.c_int, [MP, i32, ctypes.POINTER(sz)]),
     "chebfd_filter_query_blocks": (ctypes.c_int, [MP, i32, i32, ctypes.POINTER(sz)]),
     "chebfd_step_kernel": (ctypes.c_int, [MP, i32, ctypes.POINTER(i32)]),
+    "chebfd_step_kernel_small": (ctypes.c_int, [MP, i32, ctypes.POINTER(i32)]),
     "chebfd_filter": (ctypes.c_int, [MP, f64, f64, P, i32, i32, i32, i32, P, P, P, P, P, P, sz, P]),
     "chebfd_filter_unfused": (ctypes.c_int, [MP, f64, f64, P, i32, i32, i32, i32, P, P, P, P, P, P, sz, P]),
     "chebfd_filter_noalloc": (ctypes.c_int, [MP, f64, f64, P, i32, i32, i32, i32, P, P, P, P, P, P]),

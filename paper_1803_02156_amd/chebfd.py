@@ -170,6 +170,13 @@ def chebfd_step_kernel(H: Matrix, n_b: int) -> int:
     return k.value
 
 
+def chebfd_step_kernel_small(H: Matrix, n_b: int) -> bool:
+    """Whether KERNEL_LDS stands for its variant for small matrices."""
+    k = ctypes.c_int32()
+    check(load().chebfd_step_kernel_small(H.ref(), n_b, ctypes.byref(k)))
+    return k.value != 0
+
+
 def chebfd_filter_query(H: Matrix, n_b: int) -> int:
     b = ctypes.c_size_t()
     check(load().chebfd_filter_query(H.ref(), n_b, ctypes.byref(b)))

@@ -599,6 +599,17 @@ int chebfd_step_kernel(const chebfd_matrix *H, int32_t n_b, int32_t *kind) {
     return CHEBFD_OK;
 }
 
+int chebfd_step_kernel_small(const chebfd_matrix *H, int32_t n_b, int32_t *small) {
+    clear_error();
+    int rc;
+    if ((rc = check_handle(H)) || (rc = check_prec_nb(H->prec, n_b))) return rc;
+    CHEBFD_REQUIRE(small != nullptr, "small is NULL");
+    StepGeometry g;
+    if ((rc = filter_geometry(H, H->prec, n_b, &g))) return rc;
+    *small = g.wave ? 1 : 0;
+    return CHEBFD_OK;
+}
+
 static StepArgs base_args(const chebfd_matrix *H, double alpha, double beta) {
     StepArgs a;
     std::memset(&a, 0, sizeof(a));
