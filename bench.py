@@ -81,7 +81,14 @@ def log(msg):
 
 # fused-step kernels (chebfd_step_kernel kinds): short name, source file
 STEP_KERNELS = {0: ("cheb_lds", "filter_lds.hip"), 1: ("cheb_row", "filter_rows.hip"),
-                2: ("cheb_multirow", "filter.hip"), 3: ("cheb_win", "filter_win.hip")}
+                2: ("cheb_step", "filter.hip"), 3: ("cheb_win", "filter_win.hip")}
+SMALL_KERNEL = 4           # kind 0's variant for small matrices
+STEP_KERNELS[SMALL_KERNEL] = ("cheb_wave", "filter_wave.hip")
+
+
+def step_kernel(P, M, n_b: int) -> int:
+    """Key into STEP_KERNELS of the kernel that the filter of M launches."""
+    return SMALL_KERNEL if P.chebfd_step_kernel_small(M, n_b) else P.chebfd_step_kernel(M, n_b)
 
 
 def kernel_source_hash(kind: int) -> str:
@@ -417,7 +424,7 @@ def main():
     avg_launch_s = filt_ms * 1e-3 / n_p
     r, w = traffic.launch_bytes(n, nnz, n_b, prec)
     achieved = (r + w) / avg_launch_s / 1e9
-    kind = P.chebfd_step_kernel(M, n_b)
+    kind = step_kernel(P, M, n_b)
     op_alone_s = bf.op_alone(args.op_launches)
 
     unfused = None
@@ -471,7 +478,7 @@ def main():
         mbytes = traffic.filter_bytes(n, nnz, mb, mb, n_p, 1)
         m_avg = m_filt * 1e-3 / n_p
         rm, wm = traffic.launch_bytes(n, nnz, mb, 1)
-        mkind = P.chebfd_step_kernel(M32, mb)
+        mkind = step_kernel(P, M32, mb)
         mixed = {"value": round(mbytes / (m_step * 1e-3) / 1e9, 2), "unit": "GB/s", "ms_per_step": round(m_step, 3),
                  "n_b": mb, "steps": k, "pct_of_hbm_peak": round(100.0 * mbytes / (m_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 2),
                  "gflops": round(traffic.filter_flops(n, mb, n_p, nnz / n) / (m_step * 1e-3) / 1e9, 1),
