@@ -46,6 +46,16 @@ def filter_bytes(n: int, nnz: int, n_s: int, n_b: int, n_p: int, prec: int) -> i
     return (n_s // n_b) * ((n_p - 2) * (r + w) + r0 + w0)
 
 
+def needed_filter_bytes(n: int, nnz: int, n_s: int, n_b: int, n_p: int, prec: int) -> int:
+    """Bytes that one fused filter application has to move at least (degree n_p >= 2): the start
+    launches and n_p - 2 recurrence launches, of which those of steps 5, 8, ... and the last one
+    read and write X.  Eq. 2 (filter_bytes) counts X in every step."""
+    s = value_bytes(prec)
+    r0, w0 = start_bytes(n, nnz, n_b, prec)
+    steps, updates = n_p - 2, -(-(n_p - 2) // 3)
+    return (n_s // n_b) * (steps * (nnz * (s + 4) + 3 * n * n_b * s) + updates * 2 * n * n_b * s + r0 + w0)
+
+
 def unfused_step_bytes(n: int, nnz: int, n_b: int, prec: int) -> tuple[int, int]:
     """(read, write) bytes of one recurrence step of the unfused filter, each call
     streaming its operands once: the SpMMV W <- 2(aH+bI)U - W (matrix, U, W read;
