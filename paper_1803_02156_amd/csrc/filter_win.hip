@@ -42,7 +42,8 @@
 //   FP64 n_b = 32      68 -> 62     233 -> 216     928 -> 901
 //   c64  n_b = 64      71 -> 66     233 -> 216     924 -> 896
 //   c64  n_b = 32         -         128 -> 117     473 -> 452
-//   FP64 n_b = 16         -         141 -> 118     574 -> 476 (LDS-staged kernel before)
+//   FP64 n_b = 16         -         141 -> 118     574 -> 476 (LDS-staged kernel before, sweeps
+//                                                              in one direction)
 //
 // Lanes: TR = 1024 * 16 / (bytes of a row) rows per tile; lane t works on the
 // 16-byte vector t % LPR of row t / LPR of the tile.
@@ -535,10 +536,15 @@ bool set_win_attr() {
 bool win_geometry(const chebfd_matrix *H, int prec, int nb, int num_cus, WinGeometry *g) {
     if (H->C != 32 || H->max_width > kWinWidth) return false;
     int tr;
-    // instances where the window beats the LDS-staged kernel (measured): FP64
-    // n_b = 32, c64 n_b = 64, and rows of 256 bytes (c64 n_b = 32 and FP64 n_b = 16)
-    // from 32 tiles of 64 rows per CU (the 64x64x32 lattice: 117 and 118 against
-    // 151 and 141 us per step; 131072 rows: 31 us either way)
+    // instances where the window beats the kernels that would take the matrix otherwise
+    // (measured): FP64 n_b = 32, c64 n_b = 64, and rows of 256 bytes (FP64 n_b = 16 and
+    // c64 n_b = 32) from 32 tiles of 64 rows per CU, 524288 rows.  us per step of a
+    // degree-30 filter with moments, other kernel against window:
+    //          rows      131072    262144    294912    393216     524288    1048576
+    //   FP64 n_b = 16   31 | 37   59 | 62   77 | 71  102 | 91  136 | 110  277 | 227
+    //   c64  n_b = 32   30 | 37   54 | 61   76 | 71   98 | 89  131 | 109  265 | 220
+    // The times cross where U, W and Y leave the memory-side cache and the small-matrix
+    // kernel ends (210 MB, 273 thousand rows); the line lies above that.
     if (prec == CHEBFD_PREC_FP64 && nb == 32)
         tr = WinShape<double, 32>::TR;
     else if (prec == CHEBFD_PREC_MIXED && nb == 64)

@@ -49,8 +49,9 @@ struct StepArgs {
     double alpha, beta;
     double g0, g1, g2;
     int32_t y_terms;            // kModeStep: terms added to Y (1: g2 O', 2: g1 P too, 3: g0 O too)
-    double *part_out;           // [3*NB][G] partial dot products of this launch, or null (not wanted)
-    const double *part_in;      // [3*NB][G_prev] partials of the previous launch, or null
+    double *part_out;           // [3*NB][G] partial dot products of this launch, or null (not wanted);
+                                // small-matrix kernel: [batch][G][3*NB]
+    const double *part_in;      // partials of the previous launch (G_prev workgroups), or null
     double *red_eta;            // destination of the reduced eta (re, im pairs) [NB]
     double *red_nu;             // destination of the reduced nu [NB]
     int32_t G_prev;
@@ -87,7 +88,8 @@ int launch_lds_step(int prec, int nb, int mode, const StepArgs &a, const LdsGeom
 // own rows' matrix slots, one pass per workgroup
 constexpr int kWaveMaxWidth = 16;   // rows of at most this many stored entries
 // U, W and Y together at most this: past it they leave the 256 MB memory-side
-// cache and the LDS-staged kernel's non-temporal streams win (FP64, measured per
+// cache and the LDS-staged kernel's non-temporal streams win (the matrix is not
+// counted: its slots are read once per step in either kernel; FP64, measured per
 // step, LDS-staged against this kernel: 131072 rows n_b = 32, 201 MB, 74 and 64 us;
 // 294912 rows n_b = 16, 226 MB, 77 and 81; 98304 rows n_b = 64, 302 MB, 108 and
 // 133).  n_b = 1 takes this kernel at every size (294912 rows 26 and
