@@ -71,8 +71,8 @@ typedef struct chebfd_matrix {
     int32_t identity_perm;      /* 1 if the permutation is the identity */
     int32_t uniform_width;      /* slots per row of every chunk if all chunks are equally wide, else 0 */
     int32_t window_local[2];    /* stored entries per 1000 whose column lies in the row window of its
-                                   tile (tiles of 32 and 64 rows, window 3 tiles either side); the
-                                   filter gathers such entries from a copy of U staged in LDS */
+                                   tile (tiles of 32 rows with 3 tiles either side, tiles of 64 rows
+                                   with one); the filter gathers such entries from a copy of U staged in LDS */
     const int64_t *chunk_off;   /* [n_chunks + 1] first slot of each chunk */
     const int32_t *chunk_width; /* [n_chunks] slots per row in the chunk */
     const int32_t *col;         /* [slots] permuted column index */
@@ -163,8 +163,8 @@ int chebfd_random_phase(const chebfd_matrix *H, int32_t m, int32_t n_b, int32_t 
  * The polynomial filter (Alg. 1 on each block, Alg. 2 over the blocks):
  * d_xy (blocked layout, n_s vectors, precision `prec`) holds X on entry and
  * Y = sum_{p=0}^{n_p} gamma_p T_p(alpha H + beta I) X on return (the paper
- * overwrites X by the filtered block).  Each step p >= 3 is one launch of the
- * fused kernel (chebfd_op: recurrence W <- 2(alpha H + beta I) U - W and the dot
+ * overwrites X by the filtered block).  Each step p >= 3 of a block is one launch
+ * of the fused kernel (chebfd_op: recurrence W <- 2(alpha H + beta I) U - W and the dot
  * products eta_p = <W, U>, mu_p = <U, U> in one pass over the rows; every third
  * launch also adds the terms of the last three steps to X, in order of p).
  * d_u, d_w: n x n_b work blocks of the same precision.
@@ -173,7 +173,8 @@ int chebfd_random_phase(const chebfd_matrix *H, int32_t m, int32_t n_b, int32_t 
  *   eta[p] = <T_p x, T_{p-1} x>,  nu[p] = <T_{p-1} x, T_{p-1} x>
  * (with <a, b> = sum_i conj(a_i) b_i, FP64 accumulation, deterministic
  * summation order); row 0 is not written.  May be NULL together (moments not
- * needed is not faster: they are computed in the same pass).
+ * needed: the products are formed in the same pass all the same, but their sums
+ * over workgroups are neither stored nor reduced).
  * d_work: at least chebfd_filter_query bytes (the partial sums of the dot
  * products and one progress word per workgroup of the window kernel, tagged per
  * launch, so nothing has to start at zero).  With chebfd_filter_query_blocks
@@ -229,7 +230,8 @@ int chebfd_filter(const chebfd_matrix *H, double alpha, double beta, const doubl
  * + g1 U + g2 W as a scal and two axpby).  Arguments, layouts, outputs,
  * workspace (chebfd_filter_query bytes) and errors as chebfd_filter; results
  * equal it up to rounding order.  Each extra call moves its operands through
- * HBM again: about 1.7x the bytes of the fused step at n_b = 32.
+ * HBM again: about 2.3x the bytes of a fused step at n_b = 32 (9 block rows
+ * against 3 2/3).
  */
 int chebfd_filter_unfused(const chebfd_matrix *H, double alpha, double beta, const double *h_gamma,
                           int32_t n_p, int32_t n_s, int32_t n_b, int32_t prec, void *d_xy, void *d_u,
@@ -243,14 +245,16 @@ int chebfd_filter_unfused(const chebfd_matrix *H, double alpha, double beta, con
  * hand from one launch to the next, and the window kernel's progress words,
  * live in a static device array of 4 MiB
  * (one copy per device, held until the process ends).  Every call on a device
- * shares that device's array: calls that overlap on one device (on different
- * streams, or from several threads) race; calls in sequence on a stream are
+ * shares that device's array: calls with moments that overlap on one device (on
+ * different streams, or from several threads) race on their sums (the array never
+ * holds blocks of the search space); calls in sequence on a stream are
  * safe, since each launch overwrites the partials it later reads and nothing
  * has to start at zero.  Returns CHEBFD_EWORKSPACE, touching nothing, when
  * the launch geometry for H and n_b needs more than the array holds
  * (chebfd_filter_query bytes > 4 MiB: large n_b with many resident
  * workgroups).  Allocates nothing; other arguments, results and errors as
- * chebfd_filter (the same kernels in the same order: bitwise equal results).
+ * chebfd_filter with chebfd_filter_query bytes (the blocks one after the other,
+ * bitwise equal results).
  */
 int chebfd_filter_noalloc(const chebfd_matrix *H, double alpha, double beta, const double *h_gamma,
                           int32_t n_p, int32_t n_s, int32_t n_b, int32_t prec, void *d_xy, void *d_u,
@@ -358,9 +362,10 @@ int chebfd_tsqr(int64_t n, int32_t m, int32_t n_b, int32_t prec, const void *d_y
 
 /*
  * Eigendecomposition of a Hermitian m x m FP64 complex matrix (m <= 512) by
- * cyclic Jacobi rotations (one launch per round of disjoint rotations, one
- * workgroup per rotation pair): d_w receives the eigenvalues in
- * ascending order, d_v (ldv) the eigenvectors; d_a (lda) is overwritten.
+ * cyclic Jacobi rotations (m <= 64: all sweeps in one launch of one workgroup;
+ * above that one launch per round of disjoint rotations, one workgroup per
+ * rotation pair): d_w receives the eigenvalues in ascending order, d_v (ldv) the
+ * eigenvectors; d_a (lda) may be overwritten (it is for m > 64).
  * Synchronises `stream`; CHEBFD_ENUMERIC if 40 sweeps do not reduce the
  * off-diagonal Frobenius norm below 4 m 2^-53 of the matrix's.
  */
@@ -427,7 +432,7 @@ typedef struct chebfd_stats {
     int32_t iterations, n_found, n_kept, status;
     double count_est;       /* eigenvalue count estimate from the first filter's moments */
     double t_total, t_filter, t_orth, t_rr, t_resid;  /* seconds (HIP events) */
-    double filter_bytes;    /* algorithmic bytes of all filter applications */
+    double filter_bytes;    /* Eq. 2's bytes of all filter applications (five block rows per step) */
 } chebfd_stats;
 
 int chebfd_solve_query(const chebfd_matrix *H, const chebfd_matrix *H64, const chebfd_params *p,
