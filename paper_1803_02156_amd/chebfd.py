@@ -197,7 +197,9 @@ class FilterWork:
         dev = H.buf.device
         self.u = torch.empty((H.n, n_b), dtype=dt, device=dev)
         self.w = torch.empty((H.n, n_b), dtype=dt, device=dev)
-        self.nbytes = chebfd_filter_query_blocks(H, n_s, n_b)
+        # whole blocks of n_s (also where it holds none: single steps use the buffers too)
+        blocks = max(n_s // max(n_b, 1), 1)
+        self.nbytes = chebfd_filter_query_blocks(H, blocks * n_b, n_b)
         self.work = device_buffer(self.nbytes, dev)
         self.eta = torch.zeros((n_p + 1, n_s), dtype=torch.complex128, device=dev) if moments else None
         self.nu = torch.zeros((n_p + 1, n_s), dtype=torch.float64, device=dev) if moments else None

@@ -22,6 +22,18 @@ def P():
     return P
 
 
+def test_work_buffers_without_whole_blocks(P):
+    """The buffers of single steps: n_s need not be a multiple of n_b."""
+    M = P.chebfd_matrix_build(*topi_csr(5, 4, 3, m=1.0, W=1.5, seed=5))
+    for n_s in (0, 1, 31):
+        w = P.FilterWork(M, 32, 4, n_s)
+        assert w.nbytes == P.chebfd_filter_query(M, 32) and w.u.shape == (M.n, 32) and w.eta.shape == (5, n_s)
+    assert P.FilterWork(M, 32, 4, 33 + 32).nbytes == P.chebfd_filter_query_blocks(M, 64, 32)
+    for n_b in (0, 3):
+        with pytest.raises(P.ChebfdError):
+            P.FilterWork(M, n_b, 4, 12)
+
+
 @pytest.mark.parametrize("dims,prec,n_b,blocks", [((16, 16, 8), 0, 32, 2), ((5, 4, 3), 0, 32, 11), ((7, 5, 3), 1, 8, 3)])
 def test_one_block_and_batched_workspaces(P, dims, prec, n_b, blocks):
     M = P.chebfd_matrix_build(*topi_csr(*dims, m=1.0, W=1.5, seed=5), prec=prec)
